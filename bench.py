@@ -63,7 +63,7 @@ def log(msg):
 
 def kernel_source_hash():
     h = hashlib.sha256()
-    for f in ("fdtd_kernels.hip", "fdtd_dev.h"):
+    for f in ("fdtd_kernels.hip", "fdtd_pass.hip", "fdtd_dev.h"):
         with open(os.path.join(ROOT, "paper_2609_30039_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -126,6 +126,7 @@ def run_forward(spec, dtype, stream, K, Wm, tile=None, graph_chunk=32):
     return sim, el, kms, nl
 
 
+ONEPASS = [{"kernel": "onepass", "tile_rows": 0, "tile_kz": 0}]
 SPLIT_SHAPES = [{"kernel": "split", "tile_rows": r, "tile_kz": z} for (r, z) in ((8, 2), (8, 3), (8, 4), (8, 8), (0, 8))]
 
 
@@ -144,7 +145,7 @@ def headline(args, stream, khash):
         kk, rr, zz = args.shape.split(",")
         tile = {"kernel": kk, "tile_rows": int(rr), "tile_kz": int(zz)}
     else:
-        tile = AT.tune(spec, "f32", stream=stream, log=log, steps=3, candidates=SPLIT_SHAPES[2:4])
+        tile = AT.tune(spec, "f32", stream=stream, log=log, steps=3, candidates=SPLIT_SHAPES[2:4] + ONEPASS)
     K, Wm = args.steps, args.warmup
     log(f"headline: anisotropic_lorentz {spec.shape} FP32, {BENCH_STEP} time steps per step, warmup {Wm}, "
         f"timed {K}, launch shape {tile}")
@@ -203,8 +204,8 @@ def headline(args, stream, khash):
                      "traffic": None if traffic is None else round(traffic / (avg_ms * 1e-3) / 1e9, 1),
                      "kernel": {"split": "split E and H kernels (k_fwd_e with the Lorentz-box blocks leading, "
                                          "then k_fwd_h)",
-                                "onepass": "single-pass interior kernel k_fwd_one beside the split E and H kernels "
-                                           "on the absorbing, wall and dispersive blocks",
+                                "onepass": "single-pass kernel k_pass: E and H of a step in one z-marching launch (the "
+                                           "dispersive box in k_fwd_lor before it)",
                                 "fused": "fused single-pass tile kernels"}[tile["kernel"]]
                                + ": all stepping launches of one time step",
                      "launch_shape": tile,

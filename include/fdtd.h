@@ -93,14 +93,17 @@ enum { FDTD_EX = 0, FDTD_EY, FDTD_EZ, FDTD_HX, FDTD_HY, FDTD_HZ, FDTD_ADJ = 6 };
 enum { FDTD_RECORD = 1u, FDTD_REPLAY = 2u };
 /* monitor ops */
 enum { FDTD_MON_GET = 0, FDTD_MON_FLUX = 1, FDTD_MON_SET_COTANGENT = 2, FDTD_MON_RESET = 3 };
-/* kernel family.  AUTO and SPLIT: one E launch and one H launch per step,
-   updating the state in place; FUSED: one pass per step over tiles, writing
-   the other state set; ONEPASS: the split kernels on the blocks that meet an
-   absorbing slab, a wall or a dispersive box, and one z-marching pass that
-   advances E and H together on every other block (interior blocks), writing
-   the other state set.  Results are bitwise identical; the speed depends on
-   the geometry (the package's autotuner picks per workload).  ONEPASS takes
-   the split launch shapes (tile_rows 4 or 8) and no reversible mode. */
+/* kernel family.  SPLIT: one E launch and one H launch per step, updating the
+   state in place; FUSED: one pass per step over tiles, writing the other state
+   set; ONEPASS: one z-marching launch per step that advances E and H together,
+   writing the other state set, on the domains it admits (scalar or diagonal
+   permittivity; a periodic x axis with an even number of FP32 cells), the
+   split kernels on the others; AUTO: without a launch shape (tile_rows,
+   tile_kz) ONEPASS or SPLIT by the size of the state, with one SPLIT.  Results
+   are bitwise identical; the speed depends on the geometry (the package's
+   autotuner picks per workload).  ONEPASS takes tile_rows 4 or 8 (for the
+   domains on the split kernels), tile_kz planes per block (0: by size) and no
+   reversible mode. */
 enum { FDTD_KERNEL_AUTO = 0, FDTD_KERNEL_SPLIT = 1, FDTD_KERNEL_FUSED = 2, FDTD_KERNEL_ONEPASS = 3 };
 
 #define FDTD_MAX_SOURCES 4

@@ -1,6 +1,6 @@
 """Launch-shape autotuner for the stepping kernels.
 
-Candidates are the kernel family (split E/H launches or fused single pass)
+Candidates are the kernel family (split E/H launches, the single pass or the fused tiles)
 and the tile shape (register-blocked rows per wave, z planes per block).  Each
 candidate is timed through the C-ABI on a handle of the real workload (HIP
 events around the stepping launches only, monitors off), forward steps and
@@ -28,9 +28,9 @@ CANDIDATES = [
     {"kernel": "split", "tile_rows": 8, "tile_kz": 3},
     {"kernel": "split", "tile_rows": 8, "tile_kz": 4},
     {"kernel": "split", "tile_rows": 8, "tile_kz": 8},
-    {"kernel": "onepass", "tile_rows": 8, "tile_kz": 8},
-    {"kernel": "onepass", "tile_rows": 8, "tile_kz": 16},
+    {"kernel": "onepass", "tile_rows": 0, "tile_kz": 0},
     {"kernel": "onepass", "tile_rows": 0, "tile_kz": 16},
+    {"kernel": "onepass", "tile_rows": 0, "tile_kz": 32},
     {"kernel": "fused", "tile_rows": 2, "tile_kz": 8},
     {"kernel": "fused", "tile_rows": 2, "tile_kz": 16},
     {"kernel": "fused", "tile_rows": 4, "tile_kz": 8},

@@ -5,7 +5,8 @@
 //                  128 B so every row starts on a cache line;
 //   absorbers      psi slabs per face (axis a, side s) for the two components
 //                  that take a-derivatives; x faces [nz][ny][L], y faces
-//                  [nz][L][nx], z faces [L][ny][nx];
+//                  [nz][L][ppx], z faces [L][ny][ppx], ppx = nx rounded up to
+//                  even so that a pair of x nodes is aligned and stays in its row;
 //   material       eps^-1 over a box (one array for isotropic media, three for
 //                  diagonal tensors), a scalar outside;
 //   Lorentz        E^{n-1}, W^n, W^{n-1} per component over the Lorentz box.
@@ -35,6 +36,13 @@ struct SmpDev {
     int i0, i1, j0, j1, k;
     int npts, rcomp;
     void* ring;
+};
+
+// A probe as the single-pass kernel records it: the thread that owns the node
+// writes the sample of forward step t to trace[t].
+struct PrbDev {
+    int comp, i, j, k, ntrace;
+    double* trace;
 };
 
 // Global-address-space views of device pointers.  Pointers read out of a
@@ -67,6 +75,10 @@ template <typename T>
 struct DomDev {
     int n[3];                  // cells along x, y, z
     int pitch;                 // row pitch of field arrays
+    // absorber memories by pairs of x nodes: row pitch of the y and z slabs
+    // (n[0] rounded up to even), of the x slabs per side, and the high x
+    // slab's first stored node (rounded down to even)
+    int ppx, lxp[2], lxs;
     long long plane;           // pitch * ny
     T S;
     long long fs, as;          // forward / adjoint state-set strides (elements)
@@ -92,7 +104,10 @@ struct DomDev {
     int tens;
     const T* tinv[6];
     T* curl[3];
-    int onep;                  // the domain's interior blocks may take the single-pass kernel
+    int pass;                  // the domain takes the single-pass forward (fdtd_pass.hip)
+    int lorpre;                // its dispersive cells are updated by a launch before that
+    int nprb;
+    PrbDev prb[kMaxSmp];
     int has_lor;
     int llo[3], lhi[3];
     int npole;                 // poles of the dispersive box (1..kMaxPole)
@@ -151,16 +166,13 @@ __device__ __forceinline__ int slab_side(const DomDev<T>& d, int a, int x) {
 template <typename T>
 __device__ __forceinline__ long long pidx(const DomDev<T>& d, int a, int s, int i, int j, int k) {
     int L = d.L[a][s];
-    if (a == 0) {
-        int ii = s ? i - (d.n[0] - L) : i;
-        return ((long long)k * d.n[1] + j) * L + ii;
-    }
+    if (a == 0) return ((long long)k * d.n[1] + j) * d.lxp[s] + (s ? i - d.lxs : i);
     if (a == 1) {
         int jj = s ? j - (d.n[1] - L) : j;
-        return ((long long)k * L + jj) * d.n[0] + i;
+        return ((long long)k * L + jj) * d.ppx + i;
     }
     int kk = s ? k - (d.n[2] - L) : k;
-    return ((long long)kk * d.n[1] + j) * d.n[0] + i;
+    return ((long long)kk * d.n[1] + j) * d.ppx + i;
 }
 
 template <typename T>
@@ -215,6 +227,56 @@ __device__ __forceinline__ T nb_fwd(const DomDev<T>& d, const FDTD_GLOBAL T* F, 
     const long long s = a == 0 ? 1 : (long long)d.pitch;
     if (x + 1 < d.n[a]) return F[f + s];
     return d.per[a] ? d.bsign[a] * F[f - (long long)(d.n[a] - 1) * s] : T(0);
+}
+
+// Graph replays hold the step index and the two working sets on the device
+// (tdev = {t, set, other set}); the launch arguments are then offsets: t is
+// added to the index, rs and ws (0 or 1) name one of the two sets.
+__device__ __forceinline__ void graph_args(const int* __restrict__ tdev, int& t, int& rs, int& ws) {
+    if (!tdev) return;
+    t += tdev[0];
+    rs = tdev[1 + rs];
+    ws = tdev[1 + ws];
+}
+
+__device__ __forceinline__ int find_domain(const int* __restrict__ bs, int ndom, int b) {
+    int lo = 0, hi = ndom;   // bs[lo] <= b < bs[hi]
+    while (hi - lo > 1) {
+        int mid = (lo + hi) >> 1;
+        if (bs[mid] <= b) lo = mid; else hi = mid;
+    }
+    return lo;
+}
+
+// In-kernel sampling (slot >= 0): a thread whose column lies in a plane
+// monitor's rectangle writes, on the monitor plane, E^{n+1} and the new H,
+// and on the plane below (flux) the new Hx, Hy, into the ring slot.
+template <typename T>
+__device__ __forceinline__ void sample_node(const DomDev<T>& d, int slot, int i, int j, int k, T ex, T ey, T ez,
+                                            T hx, T hy, T hz) {
+    for (int q = 0; q < d.nsmp; ++q) {
+        const SmpDev& m = d.smp[q];
+        if (i < m.i0 || i >= m.i1 || j < m.j0 || j >= m.j1) continue;
+        const bool on = k == m.k, below = m.kind == 1 && k + 1 == m.k;
+        if (!on && !below) continue;
+        const long long np = m.npts;
+        FDTD_GLOBAL T* buf = gp((T*)m.ring) + (long long)slot * m.rcomp * np + (j - m.j0) * (m.i1 - m.i0) + (i - m.i0);
+        if (m.kind == 1) {
+            if (on) {
+                buf[0] = ex;
+                buf[np] = ey;
+                buf[2 * np] = hx;
+                buf[4 * np] = hy;
+                if (k == 0) buf[3 * np] = buf[5 * np] = T(0);   // no plane below
+            } else {
+                buf[3 * np] = hx;
+                buf[5 * np] = hy;
+            }
+        } else {
+            const int c = m.comp;
+            buf[0] = c == 0 ? ex : c == 1 ? ey : c == 2 ? ez : c == 3 ? hx : c == 4 ? hy : hz;
+        }
+    }
 }
 
 // ---------------------------------------------------------- forward pieces

@@ -6,8 +6,8 @@
 // registers, XCD-aware block placement and state sets that a step reads and
 // writes separately.
 //
-// Two kernel families compute bitwise-identical results (same per-node
-// functions, no implicit contraction):
+// Three kernel families compute bitwise-identical results (same per-node
+// arithmetic, no implicit contraction); the third is fdtd_pass.hip:
 //   split  one launch for the E update and one for the H update (their
 //          transposes for the adjoint); the simple reference path;
 //   fused  a single pass per step: a block of 4 waves covers 64 x-columns by
@@ -36,15 +36,6 @@ __device__ __forceinline__ int xcd_remap(int b, int nb) {
     int x = b % X, idx = b / X;
     int q = nb / X, r = nb % X;
     return (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + idx;
-}
-
-__device__ __forceinline__ int find_domain(const int* __restrict__ bs, int ndom, int b) {
-    int lo = 0, hi = ndom;   // bs[lo] <= b < bs[hi]
-    while (hi - lo > 1) {
-        int mid = (lo + hi) >> 1;
-        if (bs[mid] <= b) lo = mid; else hi = mid;
-    }
-    return lo;
 }
 
 struct Col {
@@ -200,9 +191,9 @@ __device__ __forceinline__ Cpml1<T> cpml_at(const DomDev<T>& d, int a, int x) {
 template <typename T>
 __device__ __forceinline__ int poff(const DomDev<T>& d, int a, int s, int i, int j, int k) {
     int L = d.L[a][s];
-    if (a == 0) return (k * d.n[1] + j) * L + (s ? i - (d.n[0] - L) : i);
-    if (a == 1) return (k * L + (s ? j - (d.n[1] - L) : j)) * d.n[0] + i;
-    return ((s ? k - (d.n[2] - L) : k) * d.n[1] + j) * d.n[0] + i;
+    if (a == 0) return (k * d.n[1] + j) * d.lxp[s] + (s ? i - d.lxs : i);
+    if (a == 1) return (k * L + (s ? j - (d.n[1] - L) : j)) * d.ppx + i;
+    return ((s ? k - (d.n[2] - L) : k) * d.n[1] + j) * d.ppx + i;
 }
 
 // one stretched term: psi_new = b psi + c D; D/kappa + psi_new (as stretch())
@@ -266,23 +257,6 @@ struct BlkFlags {
     bool cp, lor;
 };
 
-// A block of the single-pass family: its cells, their +x, +y, +z neighbours
-// (whose E^{n+1} its H updates read, recomputed in the block) and their
-// -x, -y, -z neighbours (whose H its E updates read) lie off every absorbing
-// slab, wall node and dispersive box, so every update there is the plain
-// Yee one.  The split kernels skip exactly these blocks in that family.
-template <typename T>
-__device__ __forceinline__ bool blk_interior(const DomDev<T>& d, int x0, int y0, int k0, int k1, int w, int nr) {
-    if (!d.onep) return false;
-    const int lo[3] = {x0, y0, k0}, hi[3] = {x0 + w, y0 + nr, k1};   // hi: the +1 neighbours, inclusive
-    bool lor = d.has_lor;
-    for (int a = 0; a < 3; ++a) {
-        if (lo[a] < max(1, d.L[a][0]) || hi[a] >= d.n[a] - d.L[a][1]) return false;
-        if (hi[a] < d.llo[a] || lo[a] >= d.lhi[a]) lor = false;
-    }
-    return !lor;
-}
-
 template <typename T>
 __device__ __forceinline__ BlkFlags blk_flags(const DomDev<T>& d, int x0, int y0, int k0, int k1, int w = 64,
                                               int nr = 4) {
@@ -327,14 +301,13 @@ __device__ __forceinline__ void cole_fetch(const DomDev<T>& d, ColE<T>& p, const
 // general per-node path with the auxiliary-differential-equation history.
 template <typename T>
 __device__ __forceinline__ void e_lor_block(const DomDev<T>* __restrict__ doms, const int* __restrict__ lbs, int ndom,
-                                           int b, int rs, int ws, int t, const int* __restrict__ tdev) {
+                                           int b, int rs, int ws, int t) {
     if (b >= lbs[ndom]) return;
     int dom = find_domain(lbs, ndom, b);
     const DomDev<T>& d = doms[dom];
     const int bx = d.lhi[0] - d.llo[0], by = d.lhi[1] - d.llo[1], bzn = d.lhi[2] - d.llo[2];
     long long q = (long long)(b - lbs[dom]) * 256 + threadIdx.x;
-    if (!d.has_lor || q >= (long long)bx * by * bzn) return;
-    if (tdev) t += *tdev;
+    if (!d.has_lor || (d.pass && !d.lorpre) || q >= (long long)bx * by * bzn) return;
     const int i = d.llo[0] + (int)(q % bx), j = d.llo[1] + (int)((q / bx) % by), k = d.llo[2] + (int)(q / ((long long)bx * by));
     const long long so = (long long)rs * d.fs, wo = (long long)ws * d.fs, pl = d.plane;
     const long long f = (long long)k * pl + (long long)j * d.pitch + i;
@@ -354,6 +327,93 @@ __device__ __forceinline__ void e_lor_block(const DomDev<T>* __restrict__ doms, 
     gp(d.E[2] + wo)[f] = ez;
 }
 
+// The dispersive cells of single-pass domains with several poles: E^{n+1} and
+// histories into set ws, where the single-pass kernel reads them.  One thread
+// per cell and component (grid y): the pole loops are chains of loads, so
+// three times the threads of one per cell keep three times as many in flight.
+template <typename T>
+__global__ void __launch_bounds__(256) k_fwd_lor(const DomDev<T>* __restrict__ doms, const int* __restrict__ lbs,
+                                                 int ndom, int rs, int ws, int t, const int* __restrict__ tdev) {
+    graph_args(tdev, t, rs, ws);
+    const int b = xcd_remap(blockIdx.x, gridDim.x), c = blockIdx.y;
+    if (b >= lbs[ndom]) return;
+    const int dom = find_domain(lbs, ndom, b);
+    const DomDev<T>& d = doms[dom];
+    const int bx = d.lhi[0] - d.llo[0], by = d.lhi[1] - d.llo[1], bzn = d.lhi[2] - d.llo[2];
+    const long long q = (long long)(b - lbs[dom]) * 256 + threadIdx.x;
+    if (!d.has_lor || !d.lorpre || q >= (long long)bx * by * bzn) return;
+    const int i = d.llo[0] + (int)(q % bx), j = d.llo[1] + (int)((q / bx) % by), k = d.llo[2] + (int)(q / ((long long)bx * by));
+    const long long so = (long long)rs * d.fs, pl = d.plane, f = fidx(d, i, j, k);
+    const FDTD_GLOBAL T* H0 = gp(d.H[0] + so);
+    const FDTD_GLOBAL T* H1 = gp(d.H[1] + so);
+    const FDTD_GLOBAL T* H2 = gp(d.H[2] + so);
+    T h0, h0m, h1, h1m;
+    // Ex: d-_y Hz - d-_z Hy ; Ey: d-_z Hx - d-_x Hz ; Ez: d-_x Hy - d-_y Hx
+    if (c == 0) {
+        h0 = H2[f], h0m = nb_back(d, H2, f, 1, j);
+        h1 = H1[f], h1m = k > 0 ? H1[f - pl] : T(0);
+    } else if (c == 1) {
+        h0 = H0[f], h0m = k > 0 ? H0[f - pl] : T(0);
+        h1 = H2[f], h1m = nb_back(d, H2, f, 0, i);
+    } else {
+        h0 = H1[f], h0m = nb_back(d, H1, f, 0, i);
+        h1 = H0[f], h1m = nb_back(d, H0, f, 1, j);
+    }
+    // the dispersive branch of e_update_v, its poles four at a time so that
+    // eight loads are in flight (past the last pole its own values, unused)
+    const long long wo = (long long)ws * d.fs, lq = lidx(d, i, j, k);
+    const FDTD_GLOBAL T* W = gp(d.lor[1][c] + so) + lq;
+    const FDTD_GLOBAL T* Wo = gp(d.lor[2][c] + so) + lq;
+    FDTD_GLOBAL T* Ww = gp(d.lor[1][c] + wo) + lq;
+    FDTD_GLOBAL T* Wow = gp(d.lor[2][c] + wo) + lq;
+    const bool live = !e_masked_d(d, c, i, j, k);
+    const T e = gp(d.E[c] + so)[f], eold = gp(d.lor[0][c] + so)[lq];
+    T en = T(0);
+    if (live) {
+        const T D0 = stretch(d, d.psiE, d.fs, rs, ws, true, (c + 1) % 3, 0, 0, i, j, k, h0 - h0m);
+        const T D1 = stretch(d, d.psiE, d.fs, rs, ws, true, (c + 2) % 3, 1, 0, i, j, k, h1 - h1m);
+        const T einf = T(1) / epsinv_at(d, c, i, j, k), invden = T(1) / (einf + T(0.25) * d.lgs);
+        T num = fma(einf, e, T(0.25) * d.lgs * eold);
+        num = fma(d.S, D0 - D1, num);
+        for (int p = 0; p < d.npole; p += 4) {
+            T w[4], wl[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const long long o = min(p + u, d.npole - 1) * d.lbox;
+                w[u] = W[o];
+                wl[u] = Wo[o];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (p + u < d.npole) num -= T(0.5) * fma(T(1) + d.lal[p + u], w[u], d.lxi[p + u] * wl[u]);
+        }
+        en = num * invden;
+        for (int s = 0; s < d.nsrc; ++s) {
+            const SrcDev<T>& sr = d.src[s];
+            if (sr.comp == c && t < sr.nwave && k == sr.k && (sr.kind == 1 || (i == sr.i && j == sr.j))) en += gp(sr.wave)[t];
+        }
+    }
+    for (int p = 0; p < d.npole; p += 4) {
+        T w[4], wl[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const long long o = min(p + u, d.npole - 1) * d.lbox;
+            w[u] = W[o];
+            wl[u] = Wo[o];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (p + u >= d.npole) break;
+            T wn = fma(d.lal[p + u], w[u], d.lxi[p + u] * wl[u]);
+            wn = fma(T(0.5) * d.lg[p + u], en - eold, wn);
+            Ww[(p + u) * d.lbox] = live ? wn : T(0);
+            Wow[(p + u) * d.lbox] = live ? w[u] : T(0);
+        }
+    }
+    gp(d.lor[0][c] + wo)[lq] = live ? e : T(0);
+    gp(d.E[c] + wo)[f] = en;
+}
+
 // Blocks [0, nlb) update the Lorentz boxes (e_lor_block; nlb is a multiple
 // of 8 so that the column blocks keep their XCD placement), the rest the
 // columns.  TENS = false serves the domains with a scalar or diagonal
@@ -363,17 +423,16 @@ __device__ __forceinline__ void e_lor_block(const DomDev<T>* __restrict__ doms, 
 template <typename T, int W, bool TENS>
 __global__ void __launch_bounds__(256) k_fwd_e(const DomDev<T>* __restrict__ doms, const int* __restrict__ bs,
                                                const int* __restrict__ xr, const int* __restrict__ lbs, int nlb,
-                                               int ndom, int kz, int rs, int ws, int t, const int* __restrict__ tdev,
-                                               int skip_interior) {
+                                               int ndom, int kz, int rs, int ws, int t,
+                                               const int* __restrict__ tdev) {
+    graph_args(tdev, t, rs, ws);
     if ((int)blockIdx.x < nlb) {
-        e_lor_block(doms, lbs, ndom, xcd_remap(blockIdx.x, nlb), rs, ws, t, tdev);
+        e_lor_block(doms, lbs, ndom, xcd_remap(blockIdx.x, nlb), rs, ws, t);
         return;
     }
     const DomDev<T>* dp;
     Col c = column<T, W>(doms, bs, ndom, kz, dp, xr, (int)blockIdx.x - nlb);
-    if (!c.ok || dp->tens != (int)TENS) return;
-    if (skip_interior && blk_interior(*dp, c.x0, c.y0, c.k0, c.k1, W, 256 / W)) return;   // the single pass takes it
-    if (tdev) t += *tdev;   // graph replays: step index held on the device
+    if (!c.ok || dp->tens != (int)TENS || dp->pass) return;   // pass: the single-pass kernel takes the domain
     const DomDev<T>& d = *dp;
     const int i = c.i, j = c.j;
     const long long so = (long long)rs * d.fs, wo = (long long)ws * d.fs, pl = d.plane;
@@ -457,178 +516,6 @@ __global__ void __launch_bounds__(256) k_fwd_e(const DomDev<T>* __restrict__ dom
     }
 }
 
-
-// ============================================================ forward, single pass
-// Interior blocks (blk_interior) advance E and H in one launch, z-marching a
-// column per thread like the split kernels, into the other state set.  At
-// plane k a thread computes E^{n+1} of its own column at plane k+1 and of
-// its +x and +y neighbour columns at plane k (the components its H update
-// reads: Ez, Ey at i+1; Ez, Ex at j+1), then H^{n+3/2} at plane k.  The
-// neighbours' E^{n+1} are recomputed rather than exchanged, so the block
-// needs no LDS and no barrier; their operands are the neighbours' own loads,
-// served by the caches.  Every update is the split kernels' arithmetic on
-// the same operands, so the result is bitwise the split family's.
-template <typename T>
-struct OneOwn {   // own column, plane p: H, H one back along x and y, E^n, eps^-1
-    T h[3], hy_xm, hz_xm, hx_ym, hz_ym, e[3], ep[3];
-};
-
-template <typename T>
-struct OneNb {    // the +x and +y columns' E-update operands at plane p
-    T hx_xp, hy_xp, hz_xp, hx_xpym, ey_xp, ez_xp, epy_xp, epz_xp;
-    T hx_yp, hy_yp, hz_yp, hy_xmyp, ex_yp, ez_yp, epx_yp, epz_yp;
-};
-
-// eps^-1 of component c at (i,j,k) from a view whose mode covers the cell
-template <typename T>
-__device__ __forceinline__ T eps1(const EpsView<T>& v, int c, int i, int j, int k) {
-    const bool in = v.mode == 1 || (v.mode == 2 && i >= v.lo[0] && i < v.hi[0] && j >= v.lo[1] && j < v.hi[1] &&
-                                    k >= v.lo[2] && k < v.hi[2]);
-    if (!in) return v.bg;
-    const int q = ((k - v.lo[2]) * v.ey + (j - v.lo[1])) * v.ex + (i - v.exa);
-    return v.p[v.diag ? c : 0][q];
-}
-
-template <typename T>
-__device__ __forceinline__ void one_own(const FDTD_GLOBAL T* const (&h)[3], const FDTD_GLOBAL T* const (&e)[3],
-                                        const EpsView<T>& ev, OneOwn<T>& o, long long f, long long P, int i, int j,
-                                        int k) {
-    o.h[0] = h[0][f];
-    o.h[1] = h[1][f];
-    o.h[2] = h[2][f];
-    o.hy_xm = h[1][f - 1];
-    o.hz_xm = h[2][f - 1];
-    o.hx_ym = h[0][f - P];
-    o.hz_ym = h[2][f - P];
-    o.e[0] = e[0][f];
-    o.e[1] = e[1][f];
-    o.e[2] = e[2][f];
-    eps_at(ev, i, j, k, o.ep);
-}
-
-template <typename T>
-__device__ __forceinline__ void one_nb(const FDTD_GLOBAL T* const (&h)[3], const FDTD_GLOBAL T* const (&e)[3],
-                                       const EpsView<T>& ev, OneNb<T>& n, long long f, long long P, int i, int j,
-                                       int k) {
-    n.hx_xp = h[0][f + 1];
-    n.hy_xp = h[1][f + 1];
-    n.hz_xp = h[2][f + 1];
-    n.hx_xpym = h[0][f + 1 - P];
-    n.ey_xp = e[1][f + 1];
-    n.ez_xp = e[2][f + 1];
-    n.epy_xp = eps1(ev, 1, i + 1, j, k);
-    n.epz_xp = eps1(ev, 2, i + 1, j, k);
-    n.hx_yp = h[0][f + P];
-    n.hy_yp = h[1][f + P];
-    n.hz_yp = h[2][f + P];
-    n.hy_xmyp = h[1][f - 1 + P];
-    n.ex_yp = e[0][f + P];
-    n.ez_yp = e[2][f + P];
-    n.epx_yp = eps1(ev, 0, i, j + 1, k);
-    n.epz_yp = eps1(ev, 2, i, j + 1, k);
-}
-
-// the sources of E_c at (i, j, k) for step t, added in the split kernel's order
-template <typename T>
-__device__ __forceinline__ T add_src(const DomDev<T>& d, int c, int i, int j, int k, int t, T v) {
-    for (int q = 0; q < d.nsrc; ++q) {
-        const SrcDev<T>& sr = d.src[q];
-        if (sr.comp == c && t < sr.nwave && k == sr.k && (sr.kind == 1 || (i == sr.i && j == sr.j)))
-            v += gp(sr.wave)[t];
-    }
-    return v;
-}
-
-template <typename T, int W>
-__global__ void __launch_bounds__(256) k_fwd_one(const DomDev<T>* __restrict__ doms, const int* __restrict__ bs,
-                                                 const int* __restrict__ xr, int ndom, int kz, int rs, int ws, int t,
-                                                 const int* __restrict__ tdev, int slot) {
-    constexpr int NR = 256 / W;
-    const DomDev<T>* dp;
-    Col c = column<T, W>(doms, bs, ndom, kz, dp, xr);
-    if (!c.ok || !blk_interior(*dp, c.x0, c.y0, c.k0, c.k1, W, NR)) return;
-    if (tdev) t += *tdev;
-    const DomDev<T>& d = *dp;
-    const int i = c.i, j = c.j, k0 = c.k0, k1 = c.k1;
-    const long long so = (long long)rs * d.fs, wo = (long long)ws * d.fs, pl = d.plane, P = d.pitch;
-    const FDTD_GLOBAL T* h[3] = {gp(d.H[0] + so), gp(d.H[1] + so), gp(d.H[2] + so)};
-    const FDTD_GLOBAL T* e[3] = {gp(d.E[0] + so), gp(d.E[1] + so), gp(d.E[2] + so)};
-    FDTD_GLOBAL T* ew[3] = {gp(d.E[0] + wo), gp(d.E[1] + wo), gp(d.E[2] + wo)};
-    FDTD_GLOBAL T* hw[3] = {gp(d.H[0] + wo), gp(d.H[1] + wo), gp(d.H[2] + wo)};
-    // the block's cells and their +1 neighbours, planes k0 .. k1
-    EpsView<T> ev = eps_view(d, c.x0, c.y0, NR + 1, k0, k1);
-    {
-        bool inside = true, outside = false;
-        const int lo[3] = {c.x0, c.y0, k0}, hi[3] = {c.x0 + W, c.y0 + NR, k1};
-        for (int a = 0; a < 3; ++a) {
-            if (lo[a] < d.elo[a] || hi[a] >= d.ehi[a]) inside = false;
-            if (hi[a] < d.elo[a] || lo[a] >= d.ehi[a]) outside = true;
-        }
-        ev.mode = outside ? 0 : (inside ? 1 : 2);
-    }
-    const T S = d.S;
-    long long f = (long long)k0 * pl + (long long)j * P + i;
-    // own E^{n+1} at plane k0, from H at k0 and k0 - 1
-    T hxm = h[0][f - pl], hym = h[1][f - pl];
-    T hx_xp_m = h[0][f - pl + 1], hy_yp_m = h[1][f - pl + P];   // the +x column's Hx, the +y column's Hy at k0 - 1
-    OneOwn<T> cu, no;
-    one_own(h, e, ev, cu, f, P, i, j, k0);
-    T ex = fma(S * cu.ep[0], (cu.h[2] - cu.hz_ym) - (cu.h[1] - hym), cu.e[0]);
-    T ey = fma(S * cu.ep[1], (cu.h[0] - hxm) - (cu.h[2] - cu.hz_xm), cu.e[1]);
-    T ez = fma(S * cu.ep[2], (cu.h[1] - cu.hy_xm) - (cu.h[0] - cu.hx_ym), cu.e[2]);
-    ex = add_src(d, 0, i, j, k0, t, ex);
-    ey = add_src(d, 1, i, j, k0, t, ey);
-    ez = add_src(d, 2, i, j, k0, t, ez);
-    T hc[3] = {cu.h[0], cu.h[1], cu.h[2]};   // own H^{n+1/2} at plane k
-    OneNb<T> nb;
-    one_own(h, e, ev, no, f + pl, P, i, j, k0 + 1);
-    one_nb(h, e, ev, nb, f, P, i, j, k0);
-    for (int k = k0; k < k1; ++k, f += pl) {
-        OneOwn<T> no2 = no;
-        OneNb<T> nn = nb;
-        if (k + 1 < k1) {   // fetch ahead: own plane k + 2, neighbour plane k + 1
-            one_own(h, e, ev, no2, f + 2 * pl, P, i, j, k + 2);
-            one_nb(h, e, ev, nn, f + pl, P, i, j, k + 1);
-        }
-        // own E^{n+1} at plane k + 1
-        T ex1 = fma(S * no.ep[0], (no.h[2] - no.hz_ym) - (no.h[1] - hc[1]), no.e[0]);
-        T ey1 = fma(S * no.ep[1], (no.h[0] - hc[0]) - (no.h[2] - no.hz_xm), no.e[1]);
-        T ez1 = fma(S * no.ep[2], (no.h[1] - no.hy_xm) - (no.h[0] - no.hx_ym), no.e[2]);
-        ex1 = add_src(d, 0, i, j, k + 1, t, ex1);
-        ey1 = add_src(d, 1, i, j, k + 1, t, ey1);
-        ez1 = add_src(d, 2, i, j, k + 1, t, ez1);
-        // the +x column's Ez, Ey and the +y column's Ez, Ex at plane k
-        T ez_xp = fma(S * nb.epz_xp, (nb.hy_xp - hc[1]) - (nb.hx_xp - nb.hx_xpym), nb.ez_xp);
-        T ey_xp = fma(S * nb.epy_xp, (nb.hx_xp - hx_xp_m) - (nb.hz_xp - hc[2]), nb.ey_xp);
-        T ez_yp = fma(S * nb.epz_yp, (nb.hy_yp - nb.hy_xmyp) - (nb.hx_yp - hc[0]), nb.ez_yp);
-        T ex_yp = fma(S * nb.epx_yp, (nb.hz_yp - hc[2]) - (nb.hy_yp - hy_yp_m), nb.ex_yp);
-        ez_xp = add_src(d, 2, i + 1, j, k, t, ez_xp);
-        ey_xp = add_src(d, 1, i + 1, j, k, t, ey_xp);
-        ez_yp = add_src(d, 2, i, j + 1, k, t, ez_yp);
-        ex_yp = add_src(d, 0, i, j + 1, k, t, ex_yp);
-        // H^{n+3/2} at plane k
-        const T hx = fma(-S, (ez_yp - ez) - (ey1 - ey), hc[0]);
-        const T hy = fma(-S, (ex1 - ex) - (ez_xp - ez), hc[1]);
-        const T hz = fma(-S, (ey_xp - ey) - (ex_yp - ex), hc[2]);
-        ew[0][f] = ex;
-        ew[1][f] = ey;
-        ew[2][f] = ez;
-        hw[0][f] = hx;
-        hw[1][f] = hy;
-        hw[2][f] = hz;
-        if (slot >= 0) sample_node(d, slot, i, j, k, ex, ey, ez, hx, hy, hz);
-        hx_xp_m = nb.hx_xp;
-        hy_yp_m = nb.hy_yp;
-        hc[0] = no.h[0];
-        hc[1] = no.h[1];
-        hc[2] = no.h[2];
-        ex = ex1;
-        ey = ey1;
-        ez = ez1;
-        no = no2;
-        nb = nn;
-    }
-}
 
 // ------------------------------------------------ tensor media, assembly pass
 // Operands of plane k of the assembly pass that are not carried over from
@@ -750,7 +637,7 @@ __global__ void __launch_bounds__(256) k_tens_e(const DomDev<T>* __restrict__ do
     const DomDev<T>* dp;
     Col c = column<T, W>(doms, bs, ndom, kz, dp, xr);
     if (!c.ok || !dp->tens || (dp->per[0] || dp->per[1]) != PER) return;
-    if (tdev) t += *tdev;
+    graph_args(tdev, t, rs, ws);
     const DomDev<T>& d = *dp;
     const int i = c.i, j = c.j;
     const long long so = (long long)rs * d.fs, wo = (long long)ws * d.fs;
@@ -890,45 +777,15 @@ __device__ __forceinline__ void colh_fetch(const DomDev<T>& d, ColH<T>& p, const
     if (cp) psi_load(d, d.psiH, so, true, cx, cy, cpml_at(d, 2, k), i, j, k, p.ps);
 }
 
-// In-kernel sampling (slot >= 0): a thread whose column lies in a plane
-// monitor's rectangle writes, on the monitor plane, E^{n+1} and the new H,
-// and on the plane below (flux) the new Hx, Hy, into the ring slot.
-template <typename T>
-__device__ __forceinline__ void sample_node(const DomDev<T>& d, int slot, int i, int j, int k, T ex, T ey, T ez,
-                                            T hx, T hy, T hz) {
-    for (int q = 0; q < d.nsmp; ++q) {
-        const SmpDev& m = d.smp[q];
-        if (i < m.i0 || i >= m.i1 || j < m.j0 || j >= m.j1) continue;
-        const bool on = k == m.k, below = m.kind == 1 && k + 1 == m.k;
-        if (!on && !below) continue;
-        const long long np = m.npts;
-        FDTD_GLOBAL T* buf = gp((T*)m.ring) + (long long)slot * m.rcomp * np + (j - m.j0) * (m.i1 - m.i0) + (i - m.i0);
-        if (m.kind == 1) {
-            if (on) {
-                buf[0] = ex;
-                buf[np] = ey;
-                buf[2 * np] = hx;
-                buf[4 * np] = hy;
-                if (k == 0) buf[3 * np] = buf[5 * np] = T(0);   // no plane below
-            } else {
-                buf[3 * np] = hx;
-                buf[5 * np] = hy;
-            }
-        } else {
-            const int c = m.comp;
-            buf[0] = c == 0 ? ex : c == 1 ? ey : c == 2 ? ez : c == 3 ? hx : c == 4 ? hy : hz;
-        }
-    }
-}
-
 template <typename T, int W>
 __global__ void __launch_bounds__(256) k_fwd_h(const DomDev<T>* __restrict__ doms, const int* __restrict__ bs,
                                                const int* __restrict__ xr, int ndom, int kz, int rs, int ws, int slot,
-                                               int skip_interior) {
+                                               const int* __restrict__ tdev) {
     const DomDev<T>* dp;
     Col c = column<T, W>(doms, bs, ndom, kz, dp, xr);
-    if (!c.ok) return;
-    if (skip_interior && blk_interior(*dp, c.x0, c.y0, c.k0, c.k1, W, 256 / W)) return;
+    if (!c.ok || dp->pass) return;
+    int t = 0;
+    graph_args(tdev, t, rs, ws);
     const DomDev<T>& d = *dp;
     const int i = c.i, j = c.j;
     const long long so = (long long)rs * d.fs, wo = (long long)ws * d.fs, pl = d.plane;
@@ -2324,7 +2181,8 @@ __global__ void k_dft(MonDev m, int n0, int count, const int* __restrict__ tdev)
 template <typename T>
 __global__ void k_probe(const DomDev<T>* __restrict__ doms, MonDev m, int cs, int n, const int* __restrict__ tdev) {
     const DomDev<T>& d = doms[m.dom];
-    if (tdev) n += *tdev;
+    int ws = 0;
+    graph_args(tdev, n, cs, ws);
     if (n < 0 || n >= m.ntrace) return;
     if (threadIdx.x == 0 && blockIdx.x == 0) {
         long long f = fidx(d, m.pi, m.pj, m.k) + cs * d.fs;
@@ -2378,10 +2236,26 @@ __global__ void k_probe_seed(const DomDev<T>* __restrict__ doms, MonDev m, int a
 }
 
 // ============================================================ utilities
-// device-resident step index of graph replays: set, or advance by the steps
-// a replay has taken
-__global__ void k_step_counter(int* __restrict__ c, int value, int add) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) *c = add ? *c + value : value;
+// device-resident arguments of graph replays: the step index and the two
+// working sets (the one holding the state first)
+__global__ void k_graph_set(int* __restrict__ c, int t, int a, int b) {
+    if (threadIdx.x == 0 && blockIdx.x == 0) {
+        c[0] = t;
+        c[1] = a;
+        c[2] = b;
+    }
+}
+
+// advanced by the steps a replay has taken (swap: they ended in the other set)
+__global__ void k_graph_advance(int* __restrict__ c, int steps, int swap) {
+    if (threadIdx.x == 0 && blockIdx.x == 0) {
+        c[0] += steps;
+        if (swap) {
+            const int a = c[1];
+            c[1] = c[2];
+            c[2] = a;
+        }
+    }
 }
 
 __global__ void __launch_bounds__(256) k_add_f64(double* __restrict__ y, const double* __restrict__ x, long long n) {
@@ -2761,25 +2635,30 @@ __global__ void __launch_bounds__(256) k_fwd_plain_nc(const DomDev<T>* __restric
 
 template <typename T>
 void launch_fwd(const LaunchCfg& c, const void* doms, int rs, int ws, int t, hipStream_t s, const int* tdev,
-                int slot) {
+                int slot, bool rec) {
     const DomDev<T>* dd = (const DomDev<T>*)doms;
     if (c.kernel == 1) {
         // one launch per pass over all blocks: a second launch for the
         // interior blocks costs more in its drain than its leaner registers win
         const int nlb = (c.nlor + 7) / 8 * 8;
-        const int sk = c.onepass;
+        if (c.npass == c.ndom) {
+            if (c.nlorpre)
+                hipLaunchKernelGGL(k_fwd_lor<T>, dim3(nlb, 3), dim3(256), 0, s, dd, c.lbs, c.ndom, rs, ws, t, tdev);
+            launch_pass<T>(c, doms, rs, ws, t, s, tdev, slot, rec);
+            return;
+        }
         if (c.ntens < c.ndom) {
             if (c.sw == 32)
                 hipLaunchKernelGGL((k_fwd_e<T, 32, false>), dim3(nlb + c.ngrid), dim3(256), 0, s, dd, c.bs, c.xr,
-                                   c.lbs, nlb, c.ndom, c.kz, rs, ws, t, tdev, sk);
+                                   c.lbs, nlb, c.ndom, c.kz, rs, ws, t, tdev);
             else
                 hipLaunchKernelGGL((k_fwd_e<T, 64, false>), dim3(nlb + c.ngrid), dim3(256), 0, s, dd, c.bs, c.xr,
-                                   c.lbs, nlb, c.ndom, c.kz, rs, ws, t, tdev, sk);
+                                   c.lbs, nlb, c.ndom, c.kz, rs, ws, t, tdev);
         }
         if (c.ntens) {   // tensor domains: curl pass, then the assembly pass
             if (c.sw == 32) {
                 hipLaunchKernelGGL((k_fwd_e<T, 32, true>), dim3(c.ngrid), dim3(256), 0, s, dd, c.bs, c.xr, c.lbs, 0,
-                                   c.ndom, c.kz, rs, ws, t, tdev, 0);
+                                   c.ndom, c.kz, rs, ws, t, tdev);
                 if (c.ntens > c.ntper)
                     hipLaunchKernelGGL((k_tens_e<T, 32, false>), dim3(c.ngrid), dim3(256), 0, s, dd, c.bs, c.xr,
                                        c.ndom, c.kz, rs, ws, t, tdev);
@@ -2788,7 +2667,7 @@ void launch_fwd(const LaunchCfg& c, const void* doms, int rs, int ws, int t, hip
                                        c.ndom, c.kz, rs, ws, t, tdev);
             } else {
                 hipLaunchKernelGGL((k_fwd_e<T, 64, true>), dim3(c.ngrid), dim3(256), 0, s, dd, c.bs, c.xr, c.lbs, 0,
-                                   c.ndom, c.kz, rs, ws, t, tdev, 0);
+                                   c.ndom, c.kz, rs, ws, t, tdev);
                 if (c.ntens > c.ntper)
                     hipLaunchKernelGGL((k_tens_e<T, 64, false>), dim3(c.ngrid), dim3(256), 0, s, dd, c.bs, c.xr,
                                        c.ndom, c.kz, rs, ws, t, tdev);
@@ -2797,20 +2676,14 @@ void launch_fwd(const LaunchCfg& c, const void* doms, int rs, int ws, int t, hip
                                        c.ndom, c.kz, rs, ws, t, tdev);
             }
         }
-        if (sk) {   // interior blocks: one pass (reads set rs only, so it may run after the E pass)
-            if (c.sw == 32)
-                hipLaunchKernelGGL((k_fwd_one<T, 32>), dim3(c.ngrid), dim3(256), 0, s, dd, c.bs, c.xr, c.ndom, c.kz,
-                                   rs, ws, t, tdev, slot);
-            else
-                hipLaunchKernelGGL((k_fwd_one<T, 64>), dim3(c.ngrid), dim3(256), 0, s, dd, c.bs, c.xr, c.ndom, c.kz,
-                                   rs, ws, t, tdev, slot);
-        }
+        // single-pass domains of a mixed batch
+        if (c.npass) launch_pass<T>(c, doms, rs, ws, t, s, tdev, slot, rec);
         if (c.sw == 32)
             hipLaunchKernelGGL((k_fwd_h<T, 32>), dim3(c.ngrid), dim3(256), 0, s, dd, c.bs, c.xr, c.ndom, c.kz, rs, ws,
-                               slot, sk);
+                               slot, tdev);
         else
             hipLaunchKernelGGL((k_fwd_h<T, 64>), dim3(c.ngrid), dim3(256), 0, s, dd, c.bs, c.xr, c.ndom, c.kz, rs, ws,
-                               slot, sk);
+                               slot, tdev);
         return;
     }
     if (c.nfgen) FDTD_ROWS_SWITCH(k_fwd_fused, c.rows, dim3(c.nfgen), dim3(256), 0, s, dd, c.tfgen, c.kz, rs, ws, t)
@@ -2865,8 +2738,12 @@ void launch_seed(const void* doms, const MonDev& m, int as_, int n, hipStream_t 
     hipLaunchKernelGGL(k_seed<T>, dim3((npts + 255) / 256), dim3(256), 0, s, (const DomDev<T>*)doms, m, as_, n);
 }
 
-void launch_step_counter(int* c, int value, bool add, hipStream_t s) {
-    hipLaunchKernelGGL(k_step_counter, dim3(1), dim3(64), 0, s, c, value, add ? 1 : 0);
+void launch_graph_set(int* c, int t, int a, int b, hipStream_t s) {
+    hipLaunchKernelGGL(k_graph_set, dim3(1), dim3(64), 0, s, c, t, a, b);
+}
+
+void launch_graph_advance(int* c, int steps, bool swap, hipStream_t s) {
+    hipLaunchKernelGGL(k_graph_advance, dim3(1), dim3(64), 0, s, c, steps, swap ? 1 : 0);
 }
 
 void launch_zero(void* p, size_t bytes, hipStream_t s) {
@@ -2971,7 +2848,7 @@ int split_blocks(int nx, int ny, int nz, int kz, int w) {
 }
 
 #define FDTD_INSTANTIATE(T)                                                                   \
-    template void launch_fwd<T>(const LaunchCfg&, const void*, int, int, int, hipStream_t, const int*, int); \
+    template void launch_fwd<T>(const LaunchCfg&, const void*, int, int, int, hipStream_t, const int*, int, bool); \
     template void launch_adj<T>(const LaunchCfg&, const void*, int, int, int, hipStream_t, int, const hipStream_t*); \
     template void launch_sample<T>(const void*, const MonDev&, int, int, hipStream_t);        \
     template void launch_dft<T>(const MonDev&, int, int, hipStream_t, const int*);            \

@@ -41,7 +41,13 @@ struct LaunchCfg {
     int nlor;
     int ntens;                 // split: domains with tensor media (two E passes)
     int ntper;                 // split: those of them with a periodic axis
-    int onepass;               // split family with the single-pass kernel on interior blocks (ping-pong sets)
+    // single-pass domains (ping-pong sets): how many, threads per block, blocks
+    // and their tile table, two int4 per block: (domain, PassMask, q0, q1) and
+    // (y0, y1, k0, k1), the column groups, rows and planes it owns (domain -1:
+    // padding)
+    int npass, pnt, pgrid;
+    int nlorpre;               // those whose dispersive cells take a launch before the pass
+    const int4* ptab;
     // split adjoint: one tile table per pass, (domain | class << 24,
     // x0 | xlen << 24, y0, k0), domains with a gradient only.  x is cut into
     // the slab zones (narrow tiles, W = 16) and the interior zone (W = 32); a
@@ -64,12 +70,24 @@ struct LaunchCfg {
 
 constexpr int kFusedWaves = 4;
 
+// tdev: when set, t, rs and ws are relative to the device-held step index and
+// working sets (graph replays)
+// slot >= 0: the split H kernel and the single-pass kernel also write every
+// plane monitor's samples of the new state into that ring slot (the fused
+// family ignores it); rec: the single-pass kernel records its domains' probes
 template <typename T>
-// tdev: when set, kernels add the device-held step index to t (graph replays)
-// slot >= 0: the split H kernel also writes every plane monitor's samples of
-// the new state into that ring slot (the fused family ignores it)
 void launch_fwd(const LaunchCfg& c, const void* doms, int rs, int ws, int t, hipStream_t s, const int* tdev = nullptr,
-                int slot = -1);
+                int slot = -1, bool rec = false);
+// the single-pass kernel over the domains that take it
+template <typename T>
+void launch_pass(const LaunchCfg& c, const void* doms, int rs, int ws, int t, hipStream_t s, const int* tdev, int slot,
+                 bool rec);
+// what a tile's E nodes (halo included) meet: slabs per axis, a dispersive box or a seam
+enum PassMask { kPassX = 1, kPassY = 2, kPassZ = 4, kPassMix = 8, kPassAll = 15 };
+constexpr int kPassMaxGroups = 272;   // column groups of a tile, halo included (coefficient tables in LDS)
+constexpr int kPassMaxRows = 112;     // rows of a tile, halo included
+constexpr int kPassMaxPlanes = 64;    // planes of a tile (one bit each in the event masks)
+template <typename T> constexpr int kPassGroup = sizeof(T) == 4 ? 2 : 1;   // x nodes per thread: 8 bytes
 template <typename T>
 // pass 0: the E-node pass (all of the fused adjoint), 1: the H-node pass of
 // the split family; cs[q]: stream of split class q of that pass
@@ -111,7 +129,10 @@ void launch_rev_step(const void* doms, int ndom, int rs, int ws, int m, long lon
 int split_blocks(int nx, int ny, int nz, int kz, int w);
 
 void launch_zero(void* p, size_t bytes, hipStream_t s);
-void launch_step_counter(int* c, int value, bool add, hipStream_t s);
+// device-held graph arguments c = {step index, set, other set}: set, or
+// advance by the steps of a replay (swap: they ended in the other set)
+void launch_graph_set(int* c, int t, int a, int b, hipStream_t s);
+void launch_graph_advance(int* c, int steps, bool swap, hipStream_t s);
 void launch_copy(const void* src, void* dst, size_t bytes, hipStream_t s);
 // y[0..n) += x[0..n) (monitor accumulators of a slab into the domain's)
 void launch_add_f64(double* y, const double* x, size_t n, hipStream_t s);

@@ -225,6 +225,8 @@ struct Handle : Base {
     std::vector<int4> atiles[kAdjClasses1 + kAdjClasses2];
     std::vector<int4> atab1, atab2;   // the tables uploaded: E-node pass, H-node pass
     int4* d_atiles = nullptr;
+    std::vector<int4> ptab;           // single-pass blocks (LaunchCfg::ptab)
+    int4* d_ptab = nullptr;
     // pool: [misc][forward sets x nsets][adjoint sets x 2][split scratch][bf16 slots]
     char* pool = nullptr;
     size_t pool_bytes = 0, misc_bytes = 0, fstride = 0, astride = 0, et_bytes = 0, bfslot = 0;
@@ -248,9 +250,9 @@ struct Handle : Base {
     int dft_block = 32;
     bool bf16 = false;
     // captured step chunks (graph_chunk > 0): the kernels read the step index
-    // from d_tstep, which the replay advances; keyed by (record, current set)
+    // and the working sets from d_tstep, which the replay advances; keyed by record
     int* d_tstep = nullptr;
-    int tstep_val = -1;                        // value d_tstep holds after the queued work (-1: unknown)
+    int tstep_val = -1, tstep_set[2] = {-1, -1};   // what d_tstep holds after the queued work (-1: unknown)
     hipStream_t cst = nullptr;                 // capture stream
     struct GraphEx {
         int key;
@@ -309,13 +311,15 @@ struct Handle : Base {
 
     char* set_ptr(int q) { return fbase + (size_t)q * fstride; }
 
+    size_t n_bs() const { return 2 * ((size_t)ndom + 1) + 16; }
+
     // ------------------------------------------------------------ tiles
     // Split kernels: prefix sums of 64 x 4 column blocks per domain.  Fused
     // kernels: tiles of 64 x-columns (62 owned) by 4R rows (4R - 2 owned) by
     // kz planes, listed as bulk when they lie inside the domain away from
     // PEC nodes, absorbers, the Lorentz box and sources, general otherwise.
     void build_tiles() {
-        bs_host.assign(2 * (ndom + 1) + 16, 0);   // [bs][lbs][per-XCD run starts, lengths]
+        bs_host.assign(n_bs(), 0);   // [bs][lbs][per-XCD run starts, lengths]
         int* lbs = bs_host.data() + ndom + 1;
         tiles_gen.clear();
         tiles_bulk.clear();
@@ -531,40 +535,16 @@ struct Handle : Base {
         cfg.na2 = (int)atab2.size();
     }
 
-    // Split column blocks in their numbering (domain by domain, x fastest, then
-    // rows, then z chunks) cut into 8 contiguous runs of equal estimated cost,
-    // one per XCD: a block meeting an absorbing slab counts twice its cells
-    // (it also moves the memories).  Contiguous runs keep neighbouring
-    // columns and planes on one L2; equal cost keeps the XCDs holding the
-    // slab-heavy ends of the domain from finishing last.
-    void split_runs() {
-        const int W = cfg.sw, NR = 256 / W, kz = cfg.kz, nb = cfg.nblk;
-        std::vector<double> cost(nb);
-        double total = 0;
-        int b = 0;
-        for (int q = 0; q < ndom; ++q) {
-            const fdtd_domain_desc& s = dh[q].desc;
-            const int nbx = (s.n[0] + W - 1) / W, nby = (s.n[1] + NR - 1) / NR, nbz = (s.n[2] + kz - 1) / kz;
-            for (int bz = 0; bz < nbz; ++bz)
-                for (int by = 0; by < nby; ++by)
-                    for (int bx = 0; bx < nbx; ++bx, ++b) {
-                        const int lo[3] = {bx * W, by * NR, bz * kz};
-                        const int hi[3] = {std::min(lo[0] + W, s.n[0]) - 1, std::min(lo[1] + NR, s.n[1]) - 1,
-                                           std::min(lo[2] + kz, s.n[2]) - 1};
-                        bool cp = false;
-                        for (int a = 0; a < 3; ++a)
-                            if (lo[a] < s.pml[2 * a] || hi[a] >= s.n[a] - s.pml[2 * a + 1]) cp = true;
-                        const double cells = (double)(hi[0] - lo[0] + 1) * (hi[1] - lo[1] + 1) * (hi[2] - lo[2] + 1);
-                        cost[b] = cells * (cp ? 2.0 : 1.0);
-                        total += cost[b];
-                    }
-        }
-        int* xs = bs_host.data() + 2 * (ndom + 1);
+    // Blocks in their numbering cut into 8 contiguous runs of equal estimated
+    // cost, one per XCD (starts xs[8], lengths xs + 8); returns the workgroups
+    // to launch (8 x the longest run).
+    static int xcd_cut(const std::vector<double>& cost, int* xs) {
         int* xl = xs + 8;
+        double total = 0, acc = 0;
+        for (double c : cost) total += c;
         for (int x = 0; x < 8; ++x) xs[x] = xl[x] = 0;
-        double acc = 0;
         int prev = -1;
-        for (int t = 0; t < nb; ++t) {
+        for (int t = 0; t < (int)cost.size(); ++t) {
             const int x = std::min(7, (int)((acc + 0.5 * cost[t]) / std::max(total, 1e-30) * 8));
             if (x != prev) {
                 xs[x] = t;
@@ -573,9 +553,36 @@ struct Handle : Base {
             xl[x]++;
             acc += cost[t];
         }
-        int len = 0;
-        for (int x = 0; x < 8; ++x) len = std::max(len, xl[x]);
-        cfg.ngrid = 8 * len;
+        return 8 * *std::max_element(xl, xl + 8);
+    }
+
+    // Split column blocks in their numbering (domain by domain, x fastest, then
+    // rows, then z chunks) in one contiguous run per XCD: a block meeting an
+    // absorbing slab counts twice its cells
+    // (it also moves the memories).  Contiguous runs keep neighbouring
+    // columns and planes on one L2; equal cost keeps the XCDs holding the
+    // slab-heavy ends of the domain from finishing last.
+    void split_runs() {
+        std::vector<double> cost;
+        cost.reserve(cfg.nblk);
+        for (int q = 0; q < ndom; ++q) block_costs(dh[q].desc, cfg.sw, 256 / cfg.sw, cfg.kz, cost);
+        cfg.ngrid = xcd_cut(cost, bs_host.data() + 2 * (ndom + 1));
+    }
+
+    static void block_costs(const fdtd_domain_desc& s, int W, int NR, int kz, std::vector<double>& cost) {
+        const int nbx = (s.n[0] + W - 1) / W, nby = (s.n[1] + NR - 1) / NR, nbz = (s.n[2] + kz - 1) / kz;
+        for (int bz = 0; bz < nbz; ++bz)
+            for (int by = 0; by < nby; ++by)
+                for (int bx = 0; bx < nbx; ++bx) {
+                    const int lo[3] = {bx * W, by * NR, bz * kz};
+                    const int hi[3] = {std::min(lo[0] + W, s.n[0]) - 1, std::min(lo[1] + NR, s.n[1]) - 1,
+                                       std::min(lo[2] + kz, s.n[2]) - 1};
+                    bool cp = false;
+                    for (int a = 0; a < 3; ++a)
+                        if (lo[a] < s.pml[2 * a] || hi[a] >= s.n[a] - s.pml[2 * a + 1]) cp = true;
+                    const double cells = (double)(hi[0] - lo[0] + 1) * (hi[1] - lo[1] + 1) * (hi[2] - lo[2] + 1);
+                    cost.push_back(cells * (cp ? 2.0 : 1.0));
+                }
     }
 
     // ------------------------------------------------------------ layout
@@ -621,8 +628,10 @@ struct Handle : Base {
             for (int a = 0; a < 3; ++a) M.take(d.tab[a], 6 * (size_t)s.n[a] * ts);
             for (int a = 0; a < 3; ++a)
                 for (int side = 0; side < 2; ++side) {
+                    // (the single-pass kernel relies on this order: the arrays of
+                    // one axis side by side, at one distance per side)
                     size_t L = (size_t)s.pml[2 * a + side];
-                    size_t ne = a == 0 ? L * ny * nz : (a == 1 ? L * nx * nz : L * nx * ny);
+                    size_t ne = !L ? 0 : a == 0 ? (size_t)d.lxp[side] * ny * nz : L * (size_t)d.ppx * (a == 1 ? nz : ny);
                     for (int r = 0; r < 2; ++r) {
                         if (!ne) continue;
                         fst(d.psiE[a][side][r], ne);
@@ -690,10 +699,13 @@ struct Handle : Base {
                 }
             }
             if (asg) {   // plane monitors as the split H kernel samples them
-                d.nsmp = 0;
+                d.nsmp = d.nprb = 0;
                 for (auto& mh : h.mons) {
                     const MonDev& md = mh.dev;
-                    if (md.kind == 0) continue;
+                    if (md.kind == 0) {
+                        d.prb[d.nprb++] = PrbDev{md.comp, md.pi, md.pj, md.k, md.ntrace, md.trace};
+                        continue;
+                    }
                     SmpDev& sm = d.smp[d.nsmp++];
                     sm.kind = md.kind;
                     sm.comp = md.comp;
@@ -708,9 +720,11 @@ struct Handle : Base {
                 }
             }
         }
+        F.off += 256;   // the single-pass kernel loads pairs of histories up to one node past their end
         M.take(d_doms, sizeof(DomDev<T>) * ndom);
-        M.take(d_bs, sizeof(int) * (2 * (ndom + 1) + 16));
-        M.take(d_tstep, sizeof(int));
+        M.take(d_bs, sizeof(int) * n_bs());
+        M.take(d_tstep, 3 * sizeof(int));
+        M.take(d_ptab, sizeof(int4) * std::max<size_t>(1, ptab.size()));
         M.take(d_atiles, sizeof(int4) * std::max<size_t>(1, atab1.size() + atab2.size()));
         M.take(d_tiles, sizeof(int4) * std::max<size_t>(1, tiles_gen.size() + tiles_bulk.size() + tiles_fgen.size() +
                                                                tiles_fcp.size() + tiles_fplain.size()));
@@ -741,7 +755,6 @@ struct Handle : Base {
             return fail(FDTD_E_INVALID, "tile_rows must be 2, 4 or 8");
         if (o->tile_kz < 0) return fail(FDTD_E_INVALID, "tile_kz");
         cfg.kernel = o->kernel == FDTD_KERNEL_FUSED ? 2 : 1;
-        cfg.onepass = o->kernel == FDTD_KERNEL_ONEPASS ? 1 : 0;
         cfg.rows = o->tile_rows ? o->tile_rows : 2;
         // split family: tile_rows = rows per block, 4 (64 columns) or 8 (32 columns)
         if (cfg.kernel == 1 && o->tile_rows != 0 && o->tile_rows != 4 && o->tile_rows != 8)
@@ -782,6 +795,21 @@ struct Handle : Base {
             }
         }
         nsets = 2 + (bf16 ? 0 : o->n_ckpt);
+        if (o->kernel == FDTD_KERNEL_AUTO) {
+            // In-place stepping keeps one working set in the last-level cache
+            // (256 MB) where the single pass needs two.  With fields of 120 to
+            // 236 MB one set stays and two do not, and the split pair is the
+            // faster (us per step, split against single pass): 140^3 f64 111
+            // against 119, 160^3 f64 139 and 155, 180^3 f32 109 and 130, 190^3
+            // f32 115 and 146; outside it 130^3 f64 116 and 100, 170^3 f64 228
+            // and 195, 160^3 f32 99 and 80, 212^3 f32 240 and 190.
+            double b = 0;
+            for (int q = 0; q < n; ++q)
+                if (dd[q].pass) b += 6.0 * (double)dh[q].nfield * sizeof(T);
+            if (b >= 120e6 && b < 236e6)
+                for (auto& d : dd) d.pass = 0;
+        }
+        plan_pass();
         build_tiles();
         // ---- size the arenas
         Arena M, F, A, X;
@@ -844,6 +872,7 @@ struct Handle : Base {
         cfg.bs = d_bs;
         cfg.lbs = d_bs + ndom + 1;
         cfg.xr = d_bs + 2 * (ndom + 1);
+        cfg.ptab = d_ptab;
         cfg.tgen = d_tiles;
         cfg.tbulk = cfg.tgen + tiles_gen.size();
         cfg.tfgen = cfg.tbulk + tiles_bulk.size();
@@ -883,8 +912,7 @@ struct Handle : Base {
             }
         }
         if (hipMemcpyAsync(d_doms, dd.data(), sizeof(DomDev<T>) * n, hipMemcpyHostToDevice, st) != hipSuccess ||
-            hipMemcpyAsync(d_bs, bs_host.data(), sizeof(int) * (2 * (n + 1) + 16), hipMemcpyHostToDevice, st) !=
-                hipSuccess)
+            hipMemcpyAsync(d_bs, bs_host.data(), sizeof(int) * n_bs(), hipMemcpyHostToDevice, st) != hipSuccess)
             return fail(FDTD_E_DEVICE, "upload descriptors failed");
         {
             std::vector<int4> all(tiles_gen);
@@ -895,6 +923,9 @@ struct Handle : Base {
             if (!all.empty() && hipMemcpyAsync(d_tiles, all.data(), sizeof(int4) * all.size(), hipMemcpyHostToDevice,
                                                st) != hipSuccess)
                 return fail(FDTD_E_DEVICE, "upload tile tables failed");
+            if (!ptab.empty() && hipMemcpyAsync(d_ptab, ptab.data(), sizeof(int4) * ptab.size(), hipMemcpyHostToDevice,
+                                                st) != hipSuccess)
+                return fail(FDTD_E_DEVICE, "upload single-pass tiles failed");
             std::vector<int4> at(atab1);
             at.insert(at.end(), atab2.begin(), atab2.end());
             if (!at.empty() && hipMemcpyAsync(d_atiles, at.data(), sizeof(int4) * at.size(), hipMemcpyHostToDevice,
@@ -905,6 +936,196 @@ struct Handle : Base {
                 return fail(FDTD_E_DEVICE, "upload checkpoint table failed");
         }
         return sync("create");
+    }
+
+    // Whether a domain takes the single-pass kernel: asked for (ONEPASS), or
+    // left to the library without a split launch shape (AUTO); scalar or
+    // diagonal permittivity; a periodic x axis only with whole column groups
+    // (its seam joins the last group to the first); a group of columns meets
+    // one x slab only; planes and absorber memories within the 31-bit offsets
+    // of their buffer descriptors.  At every size measured it is the faster
+    // forward (kernels and figures: fdtd_pass.hip).
+    bool pass_admits(const fdtd_domain_desc& s, const DomDev<T>& d) const {
+        constexpr int V = kPassGroup<T>;
+        if (opt.kernel != FDTD_KERNEL_ONEPASS &&
+            !(opt.kernel == FDTD_KERNEL_AUTO && opt.tile_rows == 0 && opt.tile_kz == 0))
+            return false;
+        if (d.tens || (s.periodic[0] && s.n[0] % V)) return false;
+        if (s.n[0] - s.pml[0] - s.pml[1] < V && s.pml[0] && s.pml[1]) return false;
+        const double lim = 2147483648.0, ts = sizeof(T);
+        if (ts * d.pitch * s.n[1] >= lim) return false;
+        for (int a = 0; a < 3; ++a) {
+            const double row = a == 0 ? (double)s.n[1] * s.n[2] : (double)d.ppx * (a == 1 ? s.n[2] : s.n[1]);
+            double span = 0;
+            for (int side = 0; side < 2; ++side) span += 4.0 * (s.pml[2 * a + side] * row * ts + 256.0);
+            if (span >= lim) return false;
+        }
+        const double ebox = ts * (s.eps_hi[0] - s.eps_lo[0] + 64.0) * (s.eps_hi[1] - s.eps_lo[1]);
+        return ebox < lim;
+    }
+
+    // The x-y tiles of a single-pass domain for blocks of nt threads: (q0, q1,
+    // y0, y1) of the owned column groups and rows, at most pw groups wide and
+    // as many rows as the block holds with its halo.
+    std::vector<int4> pass_tiles(const DomDev<T>& d, int nt, int pw) const {
+        constexpr int V = kPassGroup<T>;
+        const int ny = d.n[1], nq = (d.n[0] + V - 1) / V, nbx = (nq + pw - 1) / pw;
+        std::vector<int4> out;
+        for (int x = 0; x < nbx; ++x) {
+            const int q0 = nq * x / nbx, q1 = nq * (x + 1) / nbx;
+            const int wt = q1 - q0 + (d.per[0] || q0 > 0) + (d.per[0] || q1 < nq);
+            const int rt = std::min(nt / wt, kPassMaxRows), own = ny <= rt && !d.per[1] ? ny : rt - 2;
+            const int nby = (ny + own - 1) / own;
+            for (int y = 0; y < nby; ++y)
+                out.push_back(make_int4(q0, q1, (int)((long long)ny * y / nby), (int)((long long)ny * (y + 1) / nby)));
+        }
+        return out;
+    }
+
+    // what the E nodes of a tile, halo included, meet (PassMask)
+    int pass_mask(const DomDev<T>& d, const int4& t, int k0, int k1) const {
+        constexpr int V = kPassGroup<T>;
+        const int nq = (d.n[0] + V - 1) / V;
+        const bool hr = d.per[0] || t.y < nq, ht = d.per[1] || t.w < d.n[1];
+        const int lo[3] = {t.x * V, t.z, k0};
+        const int hi[3] = {std::min((t.y + hr) * V, d.n[0]) - 1, std::min(t.w + ht, d.n[1]) - 1, std::min(k1, d.n[2] - 1)};
+        int m = 0;
+        bool lor = d.has_lor != 0;
+        for (int a = 0; a < 3; ++a) {
+            if (lo[a] < d.L[a][0] || hi[a] >= d.n[a] - d.L[a][1]) m |= 1 << a;
+            if (hi[a] < d.llo[a] || lo[a] >= d.lhi[a]) lor = false;
+        }
+        if (lor || (d.per[0] && (t.x == 0 || t.y == nq)) || (d.per[1] && (t.z == 0 || t.w == d.n[1]))) m |= kPassMix;
+        return m;
+    }
+
+    // Planes of an x-y tile's blocks: bounds of chunks of about kz planes.
+    // Small domains, whose blocks run all at once, take shorter chunks where
+    // the tile costs more per plane (slabs, dispersive cells), so that no block
+    // outlasts the others; else even ones.
+    void pass_chunks(const DomDev<T>& d, const int4& t, int kz, bool even, std::vector<int>& zb) const {
+        const int nz = d.n[2];
+        if (even) {
+            const int n = (nz + kz - 1) / kz;
+            zb.clear();
+            for (int c = 0; c <= n; ++c) zb.push_back((int)((long long)nz * c / n));
+            return;
+        }
+        int cutp[6] = {0, d.L[2][0], d.L[2][1] ? nz - d.L[2][1] - 1 : nz, nz, 0, 0}, nc = 4;
+        if (d.has_lor && (pass_mask(d, t, d.llo[2], d.lhi[2]) & kPassMix)) {
+            cutp[nc++] = std::max(0, d.llo[2] - 1);
+            cutp[nc++] = d.lhi[2];
+        }
+        std::sort(cutp, cutp + nc);
+        zb.assign(1, 0);
+        for (int q = 0; q < nc; ++q) {
+            const int to = std::min(std::max(cutp[q], 0), nz), from = zb.back();
+            if (to <= from || (to - from < 3 && to < nz && from > 0)) continue;
+            const int len = std::max(2, (int)(kz / pass_weight(pass_mask(d, t, from, to)) + 0.5));
+            const int n = std::max(1, (to - from + len / 2) / len);
+            for (int c = 1; c <= n; ++c) zb.push_back(from + (int)((long long)(to - from) * c / n));
+        }
+        if (zb.back() < nz) zb.push_back(nz);
+        for (size_t c = 0; c + 1 < zb.size(); ++c)   // the kernel's limit
+            if (zb[c + 1] - zb[c] > kPassMaxPlanes) zb.insert(zb.begin() + c + 1, zb[c] + kPassMaxPlanes);
+    }
+
+    // cost of a plane of a tile against a lean one
+    static double pass_weight(int m) {
+        double w = 1.0;
+        if (m & kPassX) w += 0.3;
+        if (m & kPassY) w += 0.3;
+        if (m & kPassZ) w += 0.3;
+        if (m & kPassMix) w += 0.8;
+        return w;
+    }
+
+    // Chooses the block and tile shape of the single-pass domains by the
+    // bytes of their fields, and lists the blocks.  Measured per step (us):
+    //                           256 threads   512 threads   1024 threads
+    //                           24 groups     67 groups     134 groups
+    //   148^3 f32, 84 MB              57            57            83
+    //   101 x 90 x 117 f64, 53 MB     37            39            50
+    //   160^3 f32, 98 MB              90            80             -
+    //   212^3 f32, 242 MB            206           187           199
+    //   280^3 f32, 542 MB            470           451           452
+    //   536^3 f32, 4.0 GB              -          3340          2450
+    // While both working sets stay in the last-level cache (256 MB) small
+    // blocks win: their barriers couple fewer waves, so the waves of an
+    // absorbing slab hold up fewer others.  Beyond it the halo rows and the
+    // short row segments of small tiles cost memory traffic.  Small domains
+    // take shorter z chunks until there are about 400 blocks (256 CUs).
+    void plan_pass() {
+        cfg.npass = cfg.nlorpre = cfg.pnt = cfg.pgrid = 0;
+        ptab.clear();
+        double bytes = 0;
+        for (int q = 0; q < ndom; ++q) {
+            if (!dd[q].pass) continue;
+            cfg.npass++;
+            bytes += 6.0 * (double)dh[q].nfield * sizeof(T);
+        }
+        if (!cfg.npass) return;
+        bool perx = false;
+        for (const auto& d : dd) perx |= d.pass && d.per[0];
+        const int shape = bytes < 90e6 ? 0 : bytes < 120e6 ? 1 : bytes < 1e9 ? 2 : 3;
+        cfg.pnt = shape == 0 ? 256 : shape < 3 ? 512 : 1024;
+        // (tiles at a periodic x axis' seam take the general variant: narrower ones confine it)
+        int pw = shape == 0 ? 24 : shape < 3 ? (perx ? 34 : 67) : 134;
+        int kz = opt.tile_kz ? std::min(opt.tile_kz, kPassMaxPlanes) : shape == 0 ? 16 : shape < 3 ? 10 : 48;
+        // Dispersive cells inline cost a round trip per plane in the waves that
+        // hold them, and several poles one per pole: those, and the wide tiles,
+        // take the launch before (148^3, 41^3 box: inline 60 us at one pole
+        // against 67, 97 against 76 at three; 536^3: 2829 against 2754).
+        for (auto& d : dd) {
+            d.lorpre = d.pass && d.has_lor && (d.npole > 1 || shape == 3);
+            cfg.nlorpre += d.lorpre;
+        }
+        std::vector<int> zb;
+        auto count = [&] {
+            size_t n = 0;
+            for (const auto& d : dd)
+                if (d.pass)
+                    for (const int4& t : pass_tiles(d, cfg.pnt, pw)) {
+                        pass_chunks(d, t, kz, shape > 1, zb);
+                        n += zb.size() - 1;
+                    }
+            return n;
+        };
+        while (!opt.tile_kz && kz > 2 && count() < 400) kz /= 2;
+        struct Blk {
+            int4 a, b;
+            double cost;
+        };
+        std::vector<Blk> tab;
+        for (int q = 0; q < ndom; ++q) {
+            const DomDev<T>& d = dd[q];
+            if (!d.pass) continue;
+            const size_t from = tab.size();
+            for (const int4& t : pass_tiles(d, cfg.pnt, pw)) {
+                pass_chunks(d, t, kz, shape > 1, zb);
+                for (size_t z = 0; z + 1 < zb.size(); ++z) {
+                    const int m = pass_mask(d, t, zb[z], zb[z + 1]);
+                    tab.push_back({make_int4(q, m, t.x, t.y), make_int4(t.z, t.w, zb[z], zb[z + 1]),
+                                   (double)(t.y - t.x + 1) * (t.w - t.z + 2) * (zb[z + 1] - zb[z] + 2) * pass_weight(m)});
+                }
+            }
+            // z chunk by z chunk, then in row bands, x fastest: blocks that run
+            // together read whole rows and share halos
+            std::stable_sort(tab.begin() + from, tab.end(), [&](const Blk& a, const Blk& b) {
+                const int za = a.b.z / kz, zc = b.b.z / kz;
+                return za != zc ? za < zc : a.b.x != b.b.x ? a.b.x < b.b.x : a.a.z < b.a.z;
+            });
+        }
+        std::vector<double> cost;
+        for (const Blk& k : tab) cost.push_back(k.cost);
+        int run[16];
+        cfg.pgrid = xcd_cut(cost, run);
+        ptab.assign(2 * (size_t)cfg.pgrid, make_int4(-1, 0, 0, 0));
+        for (int x = 0; x < 8; ++x)
+            for (int n = 0; n < run[8 + x]; ++n) {
+                ptab[2 * ((size_t)n * 8 + x)] = tab[(size_t)run[x] + n].a;
+                ptab[2 * ((size_t)n * 8 + x) + 1] = tab[(size_t)run[x] + n].b;
+            }
     }
 
     // scalar (non-pointer) fields of the device descriptor
@@ -924,8 +1145,11 @@ struct Handle : Base {
         }
         d.eps_diag = s.eps_kind == FDTD_EPS_DIAG;
         d.tens = s.eps_kind == FDTD_EPS_TENSOR;
-        // interior blocks take the single pass unless the domain has tensor media or a periodic axis
-        d.onep = opt.kernel == FDTD_KERNEL_ONEPASS && !d.tens && !s.periodic[0] && !s.periodic[1] && !s.periodic[2];
+        d.ppx = (s.n[0] + 1) & ~1;
+        d.lxp[0] = (s.pml[0] + 1) & ~1;
+        d.lxs = (s.n[0] - s.pml[1]) & ~1;
+        d.lxp[1] = (s.n[0] - d.lxs + 1) & ~1;
+        d.pass = pass_admits(s, d) ? 1 : 0;
         size_t ebox = 1;
         for (int a = 0; a < 3; ++a) {
             d.elo[a] = s.eps_lo[a];
@@ -1225,6 +1449,7 @@ struct Handle : Base {
         for (auto& h : dh)
             for (auto& mh : h.mons) {
                 if (mh.dev.kind == 0) {
+                    if (dd[mh.dev.dom].pass) continue;   // written by the single-pass kernel
                     if (n - 1 < opt.max_steps) launch_probe<T>(d_doms, mh.dev, cur, n - 1, st);
                     continue;
                 }
@@ -1255,11 +1480,11 @@ struct Handle : Base {
         return true;
     }
 
-    // Capture graph_chunk in-place split steps (with or without monitor
-    // work) into a graph: the step index comes from d_tstep, which the last
-    // node advances, so one executable serves every chunk.
+    // Capture graph_chunk steps (with or without monitor work) into a graph:
+    // the step index and the working sets come from d_tstep, which the last
+    // node advances, so one executable serves every chunk and pair of sets.
     int graph_for(bool rec, GraphEx*& out) {
-        const int key = (rec ? 1 : 0) | (cur << 1), G = opt.graph_chunk;
+        const int key = rec ? 1 : 0, G = opt.graph_chunk;
         for (auto& g : graphs)
             if (g.key == key) {
                 out = &g;
@@ -1270,22 +1495,23 @@ struct Handle : Base {
         if (hipStreamBeginCapture(cst, hipStreamCaptureModeThreadLocal) != hipSuccess)
             return fail(FDTD_E_DEVICE, "hipStreamBeginCapture failed");
         // recording chunks start with every ring empty: step s samples into slot s.
-        // In place (split), or ping-pong between the two working sets (single pass)
-        int rset = cur;
+        // In place (split), or ping-pong between the two working sets (single
+        // pass): set 0 is the one holding the state, 1 the other
+        int rset = 0;
         for (int s = 0; s < G; ++s) {
-            const int wset_ = cfg.onepass ? (wset[0] != rset ? wset[0] : wset[1]) : rset;
-            launch_fwd<T>(cfg, d_doms, rset, wset_, s, cst, d_tstep, rec ? s : -1);
-            rset = wset_;
+            const int ws = cfg.npass ? rset ^ 1 : rset;
+            launch_fwd<T>(cfg, d_doms, rset, ws, s, cst, d_tstep, rec ? s : -1, rec);
+            rset = ws;
             if (!rec) continue;
             for (auto& h : dh)
                 for (auto& mh : h.mons)
-                    if (mh.dev.kind == 0) launch_probe<T>(d_doms, mh.dev, rset, s, cst, d_tstep);
+                    if (mh.dev.kind == 0 && !dd[mh.dev.dom].pass) launch_probe<T>(d_doms, mh.dev, rset, s, cst, d_tstep);
         }
         if (rec)
             for (auto& h : dh)
                 for (auto& mh : h.mons)
                     if (mh.dev.kind != 0) launch_dft<T>(mh.dev, 1, G, cst, d_tstep);
-        launch_step_counter(d_tstep, G, true, cst);
+        launch_graph_advance(d_tstep, G, rset != 0, cst);
         GraphEx ge{key, nullptr, nullptr};
         if (hipStreamEndCapture(cst, &ge.g) != hipSuccess || !ge.g)
             return fail(FDTD_E_DEVICE, "hipStreamEndCapture failed");
@@ -1346,28 +1572,34 @@ struct Handle : Base {
         // The split kernels update a working set in place; the fused pass
         // reads neighbours' old values after they are overwritten, so it
         // writes the other set.  A restored slot is never written.
-        // (the single-pass family reads neighbours' old values across blocks:
-        // it and the split kernels beside it write the other working set)
-        const bool inplace = cfg.kernel == 1 && !cfg.onepass;
+        // (the single-pass kernel reads neighbours' old values across blocks: it
+        // and the split kernels beside it write the other working set)
+        const bool inplace = cfg.kernel == 1 && !cfg.npass;
         const int G = opt.graph_chunk;
         for (int s = 0; s < n;) {
             const bool working = cur == wset[0] || cur == wset[1];
-            if (G > 0 && cfg.kernel == 1 && (inplace || G % 2 == 0) && working && !timing_on && !opt.reversible &&
-                n - s >= G && (!rec || monitors_flushed())) {
+            if (G > 0 && cfg.kernel == 1 && working && !timing_on && !opt.reversible && n - s >= G &&
+                (!rec || monitors_flushed())) {
                 GraphEx* g = nullptr;
                 int rc = graph_for(rec, g);
                 if (rc) return rc;
-                if (tstep_val != t) launch_step_counter(d_tstep, t, false, st);
+                const int other = write_set();
+                if (tstep_val != t || tstep_set[0] != cur || tstep_set[1] != other)
+                    launch_graph_set(d_tstep, t, cur, other, st);
                 if (hipGraphLaunch(g->ex, st) != hipSuccess) return fail(FDTD_E_DEVICE, "hipGraphLaunch failed");
+                const bool swap = !inplace && G % 2;   // an odd chunk of ping-pong steps ends in the other set
+                tstep_set[0] = swap ? other : cur;
+                tstep_set[1] = swap ? cur : other;
+                cur = tstep_set[0];
                 t += G;
                 tstep_val = t;
                 s += G;
-                continue;   // an even chunk of ping-pong steps ends in the set it started from
+                continue;
             }
             int ws = inplace && working ? cur : write_set();
             const int slot = rec ? insample_slot() : -1;
             if (timing_on) ev_mark();
-            launch_fwd<T>(cfg, d_doms, cur, ws, t, st, nullptr, slot);
+            launch_fwd<T>(cfg, d_doms, cur, ws, t, st, nullptr, slot, rec);
             if (timing_on) ev_mark();
             cur = ws;
             ++t;
@@ -1773,7 +2005,7 @@ struct Streamer : StreamBase {
     fdtd_stream_options so{};
     std::vector<std::vector<double>> waves, omegas;
     hipStream_t st = nullptr;
-    int nx = 0, ny = 0, nz = 0, pitch = 0, K = 0, halo = 0, t = 0, npole = 0, ncomp_eps = 1;
+    int nx = 0, ny = 0, nz = 0, pitch = 0, ppx = 0, lxp[2] = {0, 0}, K = 0, halo = 0, t = 0, npole = 0, ncomp_eps = 1;
     std::vector<int> core;                      // core start plane of each slab; core[ns] = nz
     // One global state array: planes [z0, z1) of `per` elements each, at
     // element offset `off` of a bank.  kind: 0 field E/H c, 1 psi_E, 2 psi_H
@@ -2000,6 +2232,9 @@ struct Streamer : StreamBase {
             if (rc) return fail(rc, gh.err);
             resident_bytes = (double)gh.pool_bytes;
             pitch = gh.dd[0].pitch;
+            ppx = gh.dd[0].ppx;
+            lxp[0] = gh.dd[0].lxp[0];
+            lxp[1] = gh.dd[0].lxp[1];
             gncomp = gh.dh[0].gncomp;
             gelems = gh.dh[0].gelems;
             ncomp_eps = gh.dh[0].ncomp_eps;
@@ -2078,9 +2313,9 @@ struct Streamer : StreamBase {
                 if (!L) continue;
                 for (int r = 0; r < 2; ++r)
                     for (int kind = 1; kind <= 2; ++kind) {
-                        if (a == 0) add(kind, 0, a, side, r, 0, 0, 0, nz, (size_t)ny * L);
-                        else if (a == 1) add(kind, 0, a, side, r, 0, 0, 0, nz, (size_t)L * nx);
-                        else add(kind, 0, a, side, r, 0, 0, side ? nz - L : 0, side ? nz : L, (size_t)ny * nx);
+                        if (a == 0) add(kind, 0, a, side, r, 0, 0, 0, nz, (size_t)ny * lxp[side]);
+                        else if (a == 1) add(kind, 0, a, side, r, 0, 0, 0, nz, (size_t)L * ppx);
+                        else add(kind, 0, a, side, r, 0, 0, side ? nz - L : 0, side ? nz : L, (size_t)ny * ppx);
                     }
             }
         if (g.n_lorentz) {

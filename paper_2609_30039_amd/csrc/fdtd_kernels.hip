@@ -2268,6 +2268,32 @@ __global__ void k_fill_zero(uint32_t* __restrict__ p, long long n_words) {
     for (; q < n_words; q += stride) p[q] = 0u;
 }
 
+// Rows of a pitched array, back to back, into pinned host memory: bound by the
+// bus, so a thread gathers 16 bytes (rows need not be aligned) and stores them
+// with one write.
+template <typename W>
+__global__ __launch_bounds__(256) void k_rows_out(const W* __restrict__ src, size_t n, size_t pitch, size_t e0,
+                                                  size_t cnt, W* __restrict__ dst) {
+    constexpr int V = 16 / (int)sizeof(W);
+    const size_t i = ((size_t)blockIdx.x * blockDim.x + threadIdx.x) * V;
+    if (i >= cnt) return;
+    size_t row = (e0 + i) / n, col = (e0 + i) - row * n;
+    alignas(16) W w[V];
+#pragma unroll
+    for (int k = 0; k < V; ++k) {
+        w[k] = i + k < cnt ? src[row * pitch + col] : W(0);
+        if (++col == n) {
+            col = 0;
+            ++row;
+        }
+    }
+    if (i + V <= cnt) {
+        *(uint4*)(dst + i) = *(const uint4*)w;
+    } else {
+        for (int k = 0; i + k < cnt; ++k) dst[i + k] = w[k];
+    }
+}
+
 __global__ void k_copy_words(const uint32_t* __restrict__ src, uint32_t* __restrict__ dst, long long n_words) {
     long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     long long stride = (long long)gridDim.x * blockDim.x;
@@ -2762,6 +2788,19 @@ void launch_copy(const void* src, void* dst, size_t bytes, hipStream_t s) {
     if (nw == 0) return;
     hipLaunchKernelGGL(k_copy_words, dim3(blocks_1d(nw, 256, 8192)), dim3(256), 0, s, (const uint32_t*)src,
                        (uint32_t*)dst, nw);
+}
+
+void launch_rows_out(const void* src, size_t es, size_t n, size_t pitch, size_t e0, size_t cnt, void* dst,
+                     hipStream_t s) {
+    if (!cnt) return;
+    const size_t v = 16 / es;
+    const dim3 grid((unsigned)(((cnt + v - 1) / v + 255) / 256));
+    if (es == 4)
+        hipLaunchKernelGGL(k_rows_out<uint32_t>, grid, dim3(256), 0, s, (const uint32_t*)src, n, pitch, e0, cnt,
+                           (uint32_t*)dst);
+    else
+        hipLaunchKernelGGL(k_rows_out<uint64_t>, grid, dim3(256), 0, s, (const uint64_t*)src, n, pitch, e0, cnt,
+                           (uint64_t*)dst);
 }
 
 void launch_bf16_save(const BfArr* arr, int narr, int nblk, long long shift, float* part, unsigned int* scale,

@@ -134,6 +134,11 @@ void launch_zero(void* p, size_t bytes, hipStream_t s);
 void launch_graph_set(int* c, int t, int a, int b, hipStream_t s);
 void launch_graph_advance(int* c, int steps, bool swap, hipStream_t s);
 void launch_copy(const void* src, void* dst, size_t bytes, hipStream_t s);
+// elements [e0, e0 + cnt) of an array of rows of n elements of es bytes (4 or
+// 8), pitch elements apart at src, counted without the padding -> dst
+// (contiguous, 16-byte aligned; pinned host memory)
+void launch_rows_out(const void* src, size_t es, size_t n, size_t pitch, size_t e0, size_t cnt, void* dst,
+                     hipStream_t s);
 // y[0..n) += x[0..n) (monitor accumulators of a slab into the domain's)
 void launch_add_f64(double* y, const double* x, size_t n, hipStream_t s);
 // BF16 checkpoint slots: one table entry per forward state array (FP32)

@@ -98,9 +98,9 @@ class Simulation:
             out = np.zeros(self.max_steps)
             B.fdtd_monitor_dft(self.h, domain, monitor, B.FDTD_MON_GET, out)
             return out
-        buf = np.zeros(self._mon_shape(domain, monitor) + (2,))
-        B.fdtd_monitor_dft(self.h, domain, monitor, B.FDTD_MON_GET, buf)
-        return buf[..., 0] + 1j * buf[..., 1]
+        out = np.empty(self._mon_shape(domain, monitor), dtype=np.complex128)
+        B.fdtd_monitor_dft(self.h, domain, monitor, B.FDTD_MON_GET, out)   # (re, im) pairs
+        return out
 
     def probe(self, monitor: int, domain: int = 0, n: Optional[int] = None) -> np.ndarray:
         tr = self.spectra(monitor, domain)
@@ -120,7 +120,7 @@ class Simulation:
             buf[:len(g)] = g[:self.max_steps]
         else:
             g = np.asarray(g, dtype=np.complex128).reshape(self._mon_shape(domain, monitor))
-            buf = np.ascontiguousarray(np.stack([g.real, g.imag], axis=-1))
+            buf = np.ascontiguousarray(g).view(np.float64)   # (re, im) pairs
         B.fdtd_monitor_dft(self.h, domain, monitor, B.FDTD_MON_SET_COTANGENT, buf)
 
     def reset_monitor(self, monitor: int, domain: int = 0):
@@ -130,7 +130,7 @@ class Simulation:
         s = self.specs[domain]
         lo, hi = s.grad_box
         nc = {"diag": 3, "tensor": 6}.get(s.eps_kind, 1)
-        out = np.zeros((nc, hi[2] - lo[2], hi[1] - lo[1], hi[0] - lo[0]))
+        out = np.empty((nc, hi[2] - lo[2], hi[1] - lo[1], hi[0] - lo[0]))
         B.fdtd_get_grad(self.h, domain, out)
         return out
 
@@ -201,9 +201,9 @@ class StreamedSimulation:
             B.fdtd_stream_monitor(self.h, monitor, B.FDTD_MON_GET, out)
             return out
         i0, i1, j0, j1 = m.rect
-        buf = np.zeros((len(m.omega_dt), 4 if m.kind == "flux_z" else 1, j1 - j0, i1 - i0, 2))
-        B.fdtd_stream_monitor(self.h, monitor, B.FDTD_MON_GET, buf)
-        return buf[..., 0] + 1j * buf[..., 1]
+        out = np.empty((len(m.omega_dt), 4 if m.kind == "flux_z" else 1, j1 - j0, i1 - i0), dtype=np.complex128)
+        B.fdtd_stream_monitor(self.h, monitor, B.FDTD_MON_GET, out)   # (re, im) pairs
+        return out
 
     def flux(self, monitor: int) -> np.ndarray:
         out = np.zeros(len(self.spec.monitors[monitor].omega_dt))
@@ -220,7 +220,7 @@ class StreamedSimulation:
             i0, i1, j0, j1 = m.rect
             shape = (len(m.omega_dt), 4 if m.kind == "flux_z" else 1, j1 - j0, i1 - i0)
             g = np.asarray(g, dtype=np.complex128).reshape(shape)
-            buf = np.ascontiguousarray(np.stack([g.real, g.imag], axis=-1))
+            buf = np.ascontiguousarray(g).view(np.float64)   # (re, im) pairs
         B.fdtd_stream_set_cotangent(self.h, monitor, buf)
 
     def reverse(self):

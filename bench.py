@@ -63,7 +63,7 @@ def log(msg):
 
 def kernel_source_hash():
     h = hashlib.sha256()
-    for f in ("fdtd_kernels.hip", "fdtd_pass.hip", "fdtd_dev.h"):
+    for f in ("fdtd_kernels.hip", "fdtd_pass.hip", "fdtd_pass.h", "fdtd_adj_pass.h", "fdtd_dev.h"):
         with open(os.path.join(ROOT, "paper_2609_30039_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]

@@ -7,13 +7,15 @@ variants round identically) and packed FP32 instructions disabled.
 import os
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libfdtd.so")
-SOURCES = ["fdtd_kernels.hip", "fdtd_pass.hip", "fdtd_tens_adj.hip", "fdtd_per_adj.hip", "fdtd_runtime.cpp"]
+SOURCES = ["fdtd_kernels.hip", "fdtd_pass.hip", "fdtd_adj_pass.hip", "fdtd_adj_pass_f64.hip", "fdtd_tens_adj.hip",
+           "fdtd_per_adj.hip", "fdtd_runtime.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -21,14 +23,16 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=o
 
 
 def build(verbose: bool = False) -> str:
-    objs = []
+    cmds, objs = [], []
     for src in SOURCES:
         obj = os.path.join(CSRC, src + ".o")
         cmd = [HIPCC, "-x", "hip", *FLAGS, "-I", INCLUDE, "-I", CSRC, "-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
-        subprocess.check_call(cmd)
+        cmds.append(cmd)
         objs.append(obj)
+    with ThreadPoolExecutor(len(cmds)) as pool:   # the sources are independent
+        list(pool.map(subprocess.check_call, cmds))
     tmp = LIB + ".tmp"
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", tmp]
     if verbose:

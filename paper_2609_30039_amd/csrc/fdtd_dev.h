@@ -125,6 +125,7 @@ struct DomDev {
     SmpDev smp[kMaxSmp];
     // ---- adjoint state (set 0) ----
     int grad;                  // domain takes part in the adjoint
+    int apass;                 // by the single-pass kernel (fdtd_adj_pass.h)
     T* Ea[3];
     T* Ha[3];
     T* Et[3];                  // split transpose: cotangent of E^{n+1} after the H transpose
@@ -237,6 +238,17 @@ __device__ __forceinline__ void graph_args(const int* __restrict__ tdev, int& t,
     t += tdev[0];
     rs = tdev[1 + rs];
     ws = tdev[1 + ws];
+}
+
+// ------------------------------------------------------------ block mapping
+// Workgroups are dispatched round-robin over the 8 XCDs; remap so that each
+// XCD receives a contiguous run of logical tiles (neighbouring tiles then
+// share that XCD's L2).
+__device__ __forceinline__ int xcd_remap(int b, int nb) {
+    const int X = 8;
+    int x = b % X, idx = b / X;
+    int q = nb / X, r = nb % X;
+    return (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + idx;
 }
 
 __device__ __forceinline__ int find_domain(const int* __restrict__ bs, int ndom, int b) {

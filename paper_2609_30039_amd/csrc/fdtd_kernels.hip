@@ -27,17 +27,6 @@
 
 namespace fdtd {
 
-// ------------------------------------------------------------ block mapping
-// Workgroups are dispatched round-robin over the 8 XCDs; remap so that each
-// XCD receives a contiguous run of logical tiles (neighbouring tiles then
-// share that XCD's L2).
-__device__ __forceinline__ int xcd_remap(int b, int nb) {
-    const int X = 8;
-    int x = b % X, idx = b / X;
-    int q = nb / X, r = nb % X;
-    return (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + idx;
-}
-
 struct Col {
     int i, j, k0, k1, x0, y0;
     bool ok;

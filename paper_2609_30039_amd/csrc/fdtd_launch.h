@@ -48,6 +48,13 @@ struct LaunchCfg {
     int npass, pnt, pgrid;
     int nlorpre;               // those whose dispersive cells take a launch before the pass
     const int4* ptab;
+    // the single-pass adjoint's blocks, in the same layout with an AdjMask
+    int napass, ant, agrid;
+    const int4* atab;
+    // their gradient boxes: blocks of 256 columns by gkz planes per domain
+    // (prefix sums), all of them; nalor: a domain has dispersive cells
+    const int* gbs;
+    int ngrad, gkz, nalor;
     // split adjoint: one tile table per pass, (domain | class << 24,
     // x0 | xlen << 24, y0, k0), domains with a gradient only.  x is cut into
     // the slab zones (narrow tiles, W = 16) and the interior zone (W = 32); a
@@ -84,10 +91,19 @@ void launch_pass(const LaunchCfg& c, const void* doms, int rs, int ws, int t, hi
                  bool rec);
 // what a tile's E nodes (halo included) meet: slabs per axis, a dispersive box or a seam
 enum PassMask { kPassX = 1, kPassY = 2, kPassZ = 4, kPassMix = 8, kPassAll = 15 };
+// the single-pass adjoint: the slabs as above (met by any node, halo included), a seam, dispersive cells
+enum AdjMask { kAdjPer = 8, kAdjLor = 16, kAdjAll = 31 };
+constexpr int kAdjMaxGroups = 136;    // column groups of its tiles, halo included
 constexpr int kPassMaxGroups = 272;   // column groups of a tile, halo included (coefficient tables in LDS)
 constexpr int kPassMaxRows = 112;     // rows of a tile, halo included
 constexpr int kPassMaxPlanes = 64;    // planes of a tile (one bit each in the event masks)
 template <typename T> constexpr int kPassGroup = sizeof(T) == 4 ? 2 : 1;   // x nodes per thread: 8 bytes
+// the single-pass adjoint over the domains that take it: sets rs -> ws
+template <typename T>
+void launch_adj_pass(const LaunchCfg& c, const void* doms, int rs, int ws, hipStream_t s);
+// and the rest of their step: dJ/deps from the forward state of set fsr, then the dispersive cells
+template <typename T>
+void launch_adj_grad(const LaunchCfg& c, const void* doms, int rs, int ws, int fsr, hipStream_t s);
 template <typename T>
 // pass 0: the E-node pass (all of the fused adjoint), 1: the H-node pass of
 // the split family; cs[q]: stream of split class q of that pass

@@ -37,59 +37,11 @@
 
 #include "fdtd_dev.h"
 #include "fdtd_launch.h"
+#include "fdtd_pass.h"
 
 namespace fdtd {
 
 namespace {
-
-using Rsrc = __amdgpu_buffer_rsrc_t;
-typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-
-// an offset out of range of every descriptor here (each spans below 2 GiB)
-constexpr unsigned kOob = 0x80000000u;
-
-__device__ __forceinline__ Rsrc make_rsrc(const void* p, unsigned bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00027000);
-}
-
-// The descriptors and tables do not change during a launch: read through the
-// constant address space, their fields are scalar loads and stay scalars.
-template <typename P>
-using Const = const __attribute__((address_space(4))) P;
-template <typename P>
-__device__ __forceinline__ Const<P>* as_const(const P* p) {
-    return (Const<P>*)p;
-}
-
-template <typename T, int V>
-struct Grp {   // V neighbouring x nodes
-    T v[V];
-};
-
-template <typename T, int V>
-__device__ __forceinline__ Grp<T, V> ld_g(Rsrc r, unsigned off) {
-    static_assert(sizeof(Grp<T, V>) == 8, "8 bytes per thread");
-    return __builtin_bit_cast(Grp<T, V>, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0));
-}
-
-template <typename T, int V>
-__device__ __forceinline__ void st_g(Rsrc r, unsigned off, Grp<T, V> x) {
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, x), r, (int)off, 0, 0);
-}
-
-template <typename T>
-__device__ __forceinline__ T ld_1(Rsrc r, unsigned off) {
-    if constexpr (sizeof(T) == 4) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
-    else return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0));
-}
-
-template <typename T>
-__device__ __forceinline__ void st_1(Rsrc r, unsigned off, T x) {
-    if constexpr (sizeof(T) == 4)
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, x), r, (int)off, 0, 0);
-    else
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, x), r, (int)off, 0, 0);
-}
 
 // A group of the dispersive histories, whose rows are not aligned to groups: a
 // load may take one node before or after the box (inside the state set, which
@@ -120,13 +72,6 @@ __device__ __forceinline__ void st_u(T* p, Grp<T, V> x, const bool (&in)[V]) {
         if (in[v]) gp(p)[v] = x.v[v];
 }
 
-// barrier that orders LDS accesses only: loads and stores in flight stay so
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // LDS of a block: exchange buffers, and the absorber coefficients of its
 // columns, rows and planes (tables bE cE kiE bH cH kiH)
 template <typename T, int V, int NT>
@@ -139,29 +84,6 @@ struct PassLds {
     T cy[6][kPassMaxRows];
     T cz[6][kPassMaxPlanes + 1];
 };
-
-// One axis' absorber memories as the kernel addresses them: the eight arrays
-// of an axis (side by side: psi_E r0, psi_H r0, psi_E r1, psi_H r1 per side)
-// lie in one range of the state set, `a` bytes apart on a side.
-struct PsiAxis {
-    const char* base;     // first array of the first side present, set 0
-    unsigned span;        // bytes of all of them (0: no slab)
-    unsigned a[2];        // array distance per side
-    unsigned hi;          // offset of the high side's first array
-};
-
-template <typename D>
-__device__ __forceinline__ PsiAxis psi_range(const D& d, int a) {
-    PsiAxis p;
-    const bool lo = d.L[a][0] > 0, hi = d.L[a][1] > 0;
-    p.base = (const char*)(lo ? d.psiE[a][0][0] : d.psiE[a][1][0]);
-    p.a[0] = lo ? (unsigned)((const char*)d.psiH[a][0][0] - (const char*)d.psiE[a][0][0]) : 0u;
-    p.a[1] = hi ? (unsigned)((const char*)d.psiH[a][1][0] - (const char*)d.psiE[a][1][0]) : 0u;
-    p.hi = lo ? (unsigned)((const char*)d.psiE[a][1][0] - (const char*)d.psiE[a][0][0]) : 0u;
-    p.span = hi ? p.hi + 4u * p.a[1] : 4u * p.a[0];
-    if (!lo && !hi) p.span = 0;
-    return p;
-}
 
 // the absorber recursion of one term (as st_pref in the split kernels): in
 // the slab psi <- b psi + c D and D -> ki D + psi, outside it D unchanged
@@ -223,17 +145,17 @@ __device__ __forceinline__ void pass_march(const PassCtx<T, V>& c, PassLds<T, V,
     const char *bx = nullptr, *by = nullptr, *bz = nullptr;        // absorber memories, read set
     unsigned sx = 0, sy = 0, sz = 0, zhi = 0, za0 = 0, za1 = 0, zpl = 0;
     if constexpr (X) {
-        const PsiAxis p = psi_range(d, 0);
+        const PsiAxis p = psi_range<false>(d, 0);
         bx = p.base + c.so * (long long)ts;
         sx = p.span;
     }
     if constexpr (Y) {
-        const PsiAxis p = psi_range(d, 1);
+        const PsiAxis p = psi_range<false>(d, 1);
         by = p.base + c.so * (long long)ts;
         sy = p.span;
     }
     if constexpr (Z) {
-        const PsiAxis p = psi_range(d, 2);
+        const PsiAxis p = psi_range<false>(d, 2);
         bz = p.base + c.so * (long long)ts;
         sz = p.span;
         zhi = p.hi;
@@ -579,19 +501,6 @@ __device__ __forceinline__ void pass_march(const PassCtx<T, V>& c, PassLds<T, V,
     }
 }
 
-// a value that is the same in every lane, as a scalar
-template <typename P>
-__device__ __forceinline__ P uniform(P x) {
-    if constexpr (sizeof(P) == 4) {
-        return __builtin_bit_cast(P, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x)));
-    } else {
-        const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
-        const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)u),
-                       hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(u >> 32));
-        return __builtin_bit_cast(P, (unsigned long long)hi << 32 | lo);
-    }
-}
-
 // One tile.  A function of its own per variant (not inlined), so that the
 // lean variants do not inherit the spills and scalar pressure of the others.
 template <typename T, int V, int NT, int M, int ND>
@@ -608,57 +517,30 @@ __device__ __attribute__((noinline, noreturn)) void pass_tile(const DomDev<T>* d
     PassCtx<T, V> c;
     c.d = &d;
     c.dg = doms + dom;
-    const int nx = d.n[0], ny = d.n[1], nz = d.n[2], nq = (nx + V - 1) / V;
+    const int nx = d.n[0], ny = d.n[1], nz = d.n[2];
     const bool perx = d.per[0], pery = d.per[1];
-    const int hl = perx || q0 > 0, hr = perx || q1 < nq, hb = pery || y0 > 0, ht = pery || y1 < ny;
-    const int wt = q1 - q0 + hl + hr, rt = y1 - y0 + hb + ht;
     c.nz = nz;
     c.k0 = tab[2 * blockIdx.x + 1].z;
     c.k1 = tab[2 * blockIdx.x + 1].w;
     const int tid = c.tid = threadIdx.x;
-    // Threads take the tile's columns row by row.  A tile that meets x slabs
-    // takes the slab columns (nl low, nh high) of all rows first, so that only
-    // the waves holding them touch the x memories.
-    int nl = 0, nh = 0;
-    if constexpr (M & kPassX) {
-        const int g0 = q0 - hl;   // group of the tile's first column (no slab on a periodic axis)
-        nl = min(max((d.L[0][0] + V - 1) / V - g0, 0), wt);
-        if (d.L[0][1]) nh = min(max(g0 + wt - (nx - d.L[0][1]) / V, 0), wt - nl);
-    }
-    const int ns = nl + nh, wi = wt - ns;
-    const bool part = tid < ns * rt;   // slab columns
-    const int u = part ? tid : tid - ns * rt, wp = max(part ? ns : wi, 1);
-    c.row = u / wp;
-    const int cc = u - c.row * wp;
-    c.col = part ? (cc < nl ? cc : cc + wi) : cc + nl;
-    const bool act = (part || wi > 0) && c.row < rt;
-    if (!act) c.row = c.col = 0;   // idle threads: in range of every table, no loads, no stores
-    auto at = [&](int row, int col) {
-        return col < nl ? row * ns + col : col >= nl + wi ? row * ns + col - wi : ns * rt + row * wi + col - nl;
-    };
-    c.il = c.col > 0 ? at(c.row, c.col - 1) : 0;
-    c.ir = c.col + 1 < wt ? at(c.row, c.col + 1) : 0;
-    c.id = c.row > 0 ? at(c.row - 1, c.col) : 0;
-    c.iu = c.row + 1 < rt ? at(c.row + 1, c.col) : 0;
-    int q = q0 - hl + c.col, j = y0 - hb + c.row;
-    if (q < 0) q = nq - 1;         // across a seam (a periodic axis has whole groups)
-    else if (q >= nq) q = 0;
-    if (j < 0) j = ny - 1;
-    else if (j >= ny) j = 0;
-    const int i = q * V;
-    c.i = i;
-    c.j = j;
-    const bool has_e = act && c.row >= hb && c.col >= hl;
-    c.own = has_e && c.row < hb + (y1 - y0) && c.col < hl + (q1 - q0);
-    const unsigned f = ((unsigned)j * (unsigned)d.pitch + (unsigned)i) * (unsigned)sizeof(T);
-    c.vh = act ? f : kOob;
-    c.ve = has_e ? f : kOob;
-    c.vs = c.own ? f : kOob;
-    c.wl = i == 0 && !perx;
-    c.wr = i + V >= nx && !perx;
-    c.wd = j == 0 && !pery;
-    c.wu = j == ny - 1 && !pery;
-    c.tail = V > 1 && i + V > nx;
+    const TileMap<V> m = map_tile<T, V, (M & kPassX) != 0>(d, tid, q0, q1, y0, y1);
+    const int i = c.i = m.i, j = c.j = m.j, wt = m.wt, rt = m.rt;
+    const bool has_e = m.has_e;
+    c.row = m.row;
+    c.col = m.col;
+    c.il = m.il;
+    c.ir = m.ir;
+    c.id = m.id;
+    c.iu = m.iu;
+    c.own = m.own;
+    c.vh = m.act ? m.f : kOob;
+    c.ve = has_e ? m.f : kOob;
+    c.vs = c.own ? m.f : kOob;
+    c.wl = m.wl;
+    c.wr = m.wr;
+    c.wd = m.wd;
+    c.wu = m.wu;
+    c.tail = m.tail;
     bool any = false;
     for (int v = 0; v < V; ++v) {
         c.inb[v] = has_e && i + v >= d.elo[0] && i + v < d.ehi[0] && j >= d.elo[1] && j < d.ehi[1];
@@ -674,8 +556,8 @@ __device__ __attribute__((noinline, noreturn)) void pass_tile(const DomDev<T>* d
     c.t = t;
     c.slot = slot;
     c.src_planes = c.smp_planes = c.prb_planes = 0;
-    auto mark = [&](unsigned long long& m, int k, int last) {
-        if (k >= c.k0 && k < c.k0 + 64 && k <= last) m |= 1ull << (k - c.k0);
+    auto mark = [&](unsigned long long& b, int k, int last) {
+        if (k >= c.k0 && k < c.k0 + 64 && k <= last) b |= 1ull << (k - c.k0);
     };
     for (int s = 0; s < d.nsrc; ++s) mark(c.src_planes, d.src[s].k, c.k1);
     if (slot >= 0)
@@ -686,7 +568,7 @@ __device__ __attribute__((noinline, noreturn)) void pass_tile(const DomDev<T>* d
     if (rec)
         for (int s = 0; s < d.nprb; ++s) mark(c.prb_planes, d.prb[s].k, c.k1 - 1);
     if constexpr (M != 0) {
-            c.fl = perx && i == 0 ? d.bsign[0] : T(1);
+        c.fl = perx && i == 0 ? d.bsign[0] : T(1);
         c.fr = perx && i + V >= nx ? d.bsign[0] : T(1);
         c.fd = pery && j == 0 ? d.bsign[1] : T(1);
         c.fu = pery && j == ny - 1 ? d.bsign[1] : T(1);
@@ -694,43 +576,28 @@ __device__ __attribute__((noinline, noreturn)) void pass_tile(const DomDev<T>* d
             c.lx[v] = d.has_lor && i + v >= d.llo[0] && i + v < d.lhi[0] && j >= d.llo[1] && j < d.lhi[1];
         c.lz0 = d.has_lor ? d.llo[2] : 0;
         c.lz1 = d.has_lor ? d.lhi[2] : 0;
-        {
-            const PsiAxis p = psi_range(d, 0);
-            const int xh = nx - d.L[0][1];
-            const bool high = i + V > xh && !(i < d.L[0][0]);   // a group meets one slab only
-            bool any = false;
-            for (int v = 0; v < V; ++v) {
-                c.inx[v] = has_e && i + v < nx && (high ? i + v >= xh : i + v < d.L[0][0]);
-                any |= c.inx[v];
-            }
-            c.wx = __builtin_amdgcn_ballot_w64(any) != 0;
-        const int Ls = d.lxp[high];
-            c.ax = p.a[high];
-            c.dx = (unsigned)(ny * Ls) * (unsigned)sizeof(T);
-            c.vx = any ? (high ? p.hi : 0u) + (unsigned)(j * Ls + (high ? i - d.lxs : i)) * (unsigned)sizeof(T) : kOob;
-        }
-        {
-            const PsiAxis p = psi_range(d, 1);
-            const int yh = ny - d.L[1][1];
-            const bool high = j >= yh;
-            const int Ls = d.L[1][high];
-            c.iny = has_e && (high || j < d.L[1][0]);
-            c.wy = __builtin_amdgcn_ballot_w64(c.iny) != 0;
-            c.ay = p.a[high];
-            c.dy = (unsigned)(Ls * d.ppx) * (unsigned)sizeof(T);
-            c.vy = (high ? p.hi : 0u) + (unsigned)((high ? j - yh : j) * d.ppx + i) * (unsigned)sizeof(T);
-        }
-        c.vz = (unsigned)(j * d.ppx + i) * (unsigned)sizeof(T);
+        const SlabMap<V> sl = map_slabs<T, V, false>(d, m, has_e);
+        for (int v = 0; v < V; ++v) c.inx[v] = sl.inx[v];
+        c.iny = sl.iny;
+        c.wx = sl.wx;
+        c.wy = sl.wy;
+        c.vx = sl.vx;
+        c.dx = sl.dx;
+        c.ax = sl.ax;
+        c.vy = sl.vy;
+        c.dy = sl.dy;
+        c.ay = sl.ay;
+        c.vz = sl.vz;
         // coefficient tables of the tile into LDS
         if constexpr (M & kPassX)
             for (int s = tid; s < 6 * wt * V; s += NT) {
                 const int tb = s / (wt * V), x = s - tb * (wt * V);
-                const int gx = q0 * V - hl * V + x;
+                const int gx = (q0 - m.hl) * V + x;
                 L.cx[tb][x] = gx >= 0 && gx < nx ? gp(d.tab[0])[tb * nx + gx] : T(0);
             }
         if constexpr (M & kPassY)
             for (int s = tid; s < 6 * rt; s += NT) {
-                const int tb = s / rt, r = s - tb * rt, gy = y0 - hb + r;
+                const int tb = s / rt, r = s - tb * rt, gy = y0 - m.hb + r;
                 L.cy[tb][r] = gy >= 0 && gy < ny ? gp(d.tab[1])[tb * ny + gy] : T(0);
             }
         if constexpr (M & kPassZ) {

@@ -353,6 +353,8 @@ struct Handle : Base {
     int4* d_atiles = nullptr;
     std::vector<int4> ptab;           // single-pass blocks (LaunchCfg::ptab)
     int4* d_ptab = nullptr;
+    std::vector<int4> aptab;          // the same of the single-pass adjoint (LaunchCfg::atab)
+    int4* d_aptab = nullptr;
     // pool: [misc][forward sets x nsets][adjoint sets x 2][split scratch][bf16 slots]
     char* pool = nullptr;
     size_t pool_bytes = 0, misc_bytes = 0, fstride = 0, astride = 0, et_bytes = 0, bfslot = 0;
@@ -439,7 +441,7 @@ struct Handle : Base {
 
     char* set_ptr(int q) { return fbase + (size_t)q * fstride; }
 
-    size_t n_bs() const { return 2 * ((size_t)ndom + 1) + 16; }
+    size_t n_bs() const { return 3 * ((size_t)ndom + 1) + 16; }
 
     // ------------------------------------------------------------ tiles
     // Split kernels: prefix sums of 64 x 4 column blocks per domain.  Fused
@@ -447,7 +449,7 @@ struct Handle : Base {
     // kz planes, listed as bulk when they lie inside the domain away from
     // PEC nodes, absorbers, the Lorentz box and sources, general otherwise.
     void build_tiles() {
-        bs_host.assign(n_bs(), 0);   // [bs][lbs][per-XCD run starts, lengths]
+        bs_host.assign(n_bs(), 0);   // [bs][lbs][per-XCD run starts, lengths][gbs]
         int* lbs = bs_host.data() + ndom + 1;
         tiles_gen.clear();
         tiles_bulk.clear();
@@ -508,6 +510,25 @@ struct Handle : Base {
         }
         cfg.nblk = bs_host[ndom];
         cfg.nlor = lbs[ndom];
+        // gradient blocks of the single-pass adjoint: the carried plane saves
+        // reads where columns are long, blocks count where the boxes are small
+        // (a 64^3 box: 23 us in 128 blocks of 8 planes)
+        int* gbs = bs_host.data() + 2 * (ndom + 1) + 16;
+        cfg.nalor = 0;
+        for (cfg.gkz = 8;; cfg.gkz /= 2) {
+            for (int q = 0; q < ndom; ++q) {
+                long long nb = 0;
+                if (dd[q].apass) {
+                    const DomDev<T>& d = dd[q];
+                    nb = ((long long)(d.ghi[0] - d.glo[0]) * (d.ghi[1] - d.glo[1]) + 255) / 256 *
+                         ((d.ghi[2] - d.glo[2] + cfg.gkz - 1) / cfg.gkz);
+                }
+                gbs[q + 1] = gbs[q] + (int)nb;
+            }
+            if (gbs[ndom] >= 2048 || cfg.gkz == 1) break;
+        }
+        cfg.ngrad = gbs[ndom];
+        for (int q = 0; q < ndom; ++q) cfg.nalor += dd[q].apass && dd[q].has_lor;
         cfg.ntens = cfg.ntper = 0;
         for (int q = 0; q < ndom; ++q) {
             cfg.ntens += dd[q].tens;
@@ -538,7 +559,7 @@ struct Handle : Base {
         const int kz = cfg.kz;
         for (int q = 0; q < ndom; ++q) {
             const fdtd_domain_desc& s = dh[q].desc;
-            if (!s.grad) continue;
+            if (!s.grad || dd[q].apass) continue;
             // a periodic domain's adjoint has launches of its own (launch_per_adj)
             if (s.periodic[0] || s.periodic[1] || s.periodic[2]) continue;
             const int n[3] = {s.n[0], s.n[1], s.n[2]};
@@ -853,6 +874,7 @@ struct Handle : Base {
         M.take(d_bs, sizeof(int) * n_bs());
         M.take(d_tstep, 3 * sizeof(int));
         M.take(d_ptab, sizeof(int4) * std::max<size_t>(1, ptab.size()));
+        M.take(d_aptab, sizeof(int4) * std::max<size_t>(1, aptab.size()));
         M.take(d_atiles, sizeof(int4) * std::max<size_t>(1, atab1.size() + atab2.size()));
         M.take(d_tiles, sizeof(int4) * std::max<size_t>(1, tiles_gen.size() + tiles_bulk.size() + tiles_fgen.size() +
                                                                tiles_fcp.size() + tiles_fplain.size()));
@@ -938,6 +960,7 @@ struct Handle : Base {
                 for (auto& d : dd) d.pass = 0;
         }
         plan_pass();
+        plan_adj_pass();
         build_tiles();
         // ---- size the arenas
         Arena M, F, A, X;
@@ -1000,7 +1023,9 @@ struct Handle : Base {
         cfg.bs = d_bs;
         cfg.lbs = d_bs + ndom + 1;
         cfg.xr = d_bs + 2 * (ndom + 1);
+        cfg.gbs = d_bs + 2 * (ndom + 1) + 16;
         cfg.ptab = d_ptab;
+        cfg.atab = d_aptab;
         cfg.tgen = d_tiles;
         cfg.tbulk = cfg.tgen + tiles_gen.size();
         cfg.tfgen = cfg.tbulk + tiles_bulk.size();
@@ -1054,6 +1079,9 @@ struct Handle : Base {
             if (!ptab.empty() && hipMemcpyAsync(d_ptab, ptab.data(), sizeof(int4) * ptab.size(), hipMemcpyHostToDevice,
                                                 st) != hipSuccess)
                 return fail(FDTD_E_DEVICE, "upload single-pass tiles failed");
+            if (!aptab.empty() && hipMemcpyAsync(d_aptab, aptab.data(), sizeof(int4) * aptab.size(),
+                                                 hipMemcpyHostToDevice, st) != hipSuccess)
+                return fail(FDTD_E_DEVICE, "upload single-pass adjoint tiles failed");
             std::vector<int4> at(atab1);
             at.insert(at.end(), atab2.begin(), atab2.end());
             if (!at.empty() && hipMemcpyAsync(d_atiles, at.data(), sizeof(int4) * at.size(), hipMemcpyHostToDevice,
@@ -1127,10 +1155,36 @@ struct Handle : Base {
         return m;
     }
 
+    // the same for an adjoint tile (AdjMask): slabs met by any node, low halo
+    // included
+    int adj_mask(const DomDev<T>& d, const int4& t, int k0, int k1) const {
+        constexpr int V = kPassGroup<T>;
+        const int nq = (d.n[0] + V - 1) / V;
+        const bool hl = d.per[0] || t.x > 0, hb = d.per[1] || t.z > 0, hr = d.per[0] || t.y < nq, ht = d.per[1] || t.w < d.n[1];
+        const int lo[3] = {std::max((t.x - hl) * V, 0), std::max(t.z - hb, 0), std::max(k0 - 1, 0)};
+        const int hi[3] = {std::min((t.y + hr) * V, d.n[0]) - 1, std::min(t.w + ht, d.n[1]) - 1, std::min(k1, d.n[2] - 1)};
+        int m = 0;
+        bool lor = d.has_lor != 0;
+        for (int a = 0; a < 3; ++a) {
+            if (lo[a] < d.L[a][0] || hi[a] >= d.n[a] - d.L[a][1]) m |= 1 << a;
+            if (hi[a] < d.llo[a] || lo[a] >= d.lhi[a]) lor = false;
+        }
+        if ((d.per[0] && (t.x == 0 || t.y == nq)) || (d.per[1] && (t.z == 0 || t.w == d.n[1]))) m |= kAdjPer;
+        if (lor) return m ? (int)kAdjAll : (int)kAdjLor;
+        if (m & kAdjPer) return m & (kPassX | kPassY) ? (int)kAdjAll : m | kPassZ;
+        return m;
+    }
+
+    static double adj_weight(int m) {
+        return pass_weight(m & 7) + (m & kAdjPer ? 0.2 : 0.0) + (m & kAdjLor ? 0.4 : 0.0);
+    }
+
     // Planes of an x-y tile's blocks: bounds of chunks of about kz planes.
     // Small domains, whose blocks run all at once, take shorter chunks where
     // the tile costs more per plane (slabs, dispersive cells), so that no block
     // outlasts the others; else even ones.
+    // ADJ: of the adjoint's blocks.
+    template <bool ADJ>
     void pass_chunks(const DomDev<T>& d, const int4& t, int kz, bool even, std::vector<int>& zb) const {
         const int nz = d.n[2];
         if (even) {
@@ -1139,8 +1193,11 @@ struct Handle : Base {
             for (int c = 0; c <= n; ++c) zb.push_back((int)((long long)nz * c / n));
             return;
         }
-        int cutp[6] = {0, d.L[2][0], d.L[2][1] ? nz - d.L[2][1] - 1 : nz, nz, 0, 0}, nc = 4;
-        if (d.has_lor && (pass_mask(d, t, d.llo[2], d.lhi[2]) & kPassMix)) {
+        auto mask = [&](int k0, int k1) { return ADJ ? adj_mask(d, t, k0, k1) : pass_mask(d, t, k0, k1); };
+        auto weight = [&](int m) { return ADJ ? adj_weight(m) : pass_weight(m); };
+        // (an adjoint tile meets a slab from the plane above it on)
+        int cutp[6] = {0, d.L[2][0] + (ADJ && d.L[2][0] ? 1 : 0), d.L[2][1] ? nz - d.L[2][1] - 1 : nz, nz}, nc = 4;
+        if (d.has_lor && (mask(d.llo[2], d.lhi[2]) & (ADJ ? (int)kAdjLor : (int)kPassMix))) {
             cutp[nc++] = std::max(0, d.llo[2] - 1);
             cutp[nc++] = d.lhi[2];
         }
@@ -1149,7 +1206,7 @@ struct Handle : Base {
         for (int q = 0; q < nc; ++q) {
             const int to = std::min(std::max(cutp[q], 0), nz), from = zb.back();
             if (to <= from || (to - from < 3 && to < nz && from > 0)) continue;
-            const int len = std::max(2, (int)(kz / pass_weight(pass_mask(d, t, from, to)) + 0.5));
+            const int len = std::max(2, (int)(kz / weight(mask(from, to)) + 0.5));
             const int n = std::max(1, (to - from + len / 2) / len);
             for (int c = 1; c <= n; ++c) zb.push_back(from + (int)((long long)(to - from) * c / n));
         }
@@ -1208,18 +1265,28 @@ struct Handle : Base {
             d.lorpre = d.pass && d.has_lor && (d.npole > 1 || shape == 3);
             cfg.nlorpre += d.lorpre;
         }
+        cfg.pgrid = list_blocks<false>(cfg.pnt, pw, kz, shape > 1, opt.tile_kz == 0, ptab);
+    }
+
+    // The blocks of the single-pass domains (ADJ: of the adjoint's) for nt
+    // threads and tiles of pw groups in z chunks of about kz planes (shrink:
+    // shorter ones while there are fewer than 400), cut into runs of equal cost
+    // per XCD.  Returns the workgroups to launch.
+    template <bool ADJ>
+    int list_blocks(int nt, int pw, int kz, bool even, bool shrink, std::vector<int4>& out) const {
+        auto takes = [&](int q) { return (ADJ ? dd[q].apass : dd[q].pass) != 0; };
         std::vector<int> zb;
         auto count = [&] {
             size_t n = 0;
-            for (const auto& d : dd)
-                if (d.pass)
-                    for (const int4& t : pass_tiles(d, cfg.pnt, pw)) {
-                        pass_chunks(d, t, kz, shape > 1, zb);
+            for (int q = 0; q < ndom; ++q)
+                if (takes(q))
+                    for (const int4& t : pass_tiles(dd[q], nt, pw)) {
+                        pass_chunks<ADJ>(dd[q], t, kz, even, zb);
                         n += zb.size() - 1;
                     }
             return n;
         };
-        while (!opt.tile_kz && kz > 2 && count() < 400) kz /= 2;
+        while (shrink && kz > 2 && count() < 400) kz /= 2;
         struct Blk {
             int4 a, b;
             double cost;
@@ -1227,14 +1294,15 @@ struct Handle : Base {
         std::vector<Blk> tab;
         for (int q = 0; q < ndom; ++q) {
             const DomDev<T>& d = dd[q];
-            if (!d.pass) continue;
+            if (!takes(q)) continue;
             const size_t from = tab.size();
-            for (const int4& t : pass_tiles(d, cfg.pnt, pw)) {
-                pass_chunks(d, t, kz, shape > 1, zb);
+            for (const int4& t : pass_tiles(d, nt, pw)) {
+                pass_chunks<ADJ>(d, t, kz, even, zb);
                 for (size_t z = 0; z + 1 < zb.size(); ++z) {
-                    const int m = pass_mask(d, t, zb[z], zb[z + 1]);
+                    const int m = ADJ ? adj_mask(d, t, zb[z], zb[z + 1]) : pass_mask(d, t, zb[z], zb[z + 1]);
                     tab.push_back({make_int4(q, m, t.x, t.y), make_int4(t.z, t.w, zb[z], zb[z + 1]),
-                                   (double)(t.y - t.x + 1) * (t.w - t.z + 2) * (zb[z + 1] - zb[z] + 2) * pass_weight(m)});
+                                   (double)(t.y - t.x + 1) * (t.w - t.z + 2) * (zb[z + 1] - zb[z] + 2) *
+                                       (ADJ ? adj_weight(m) : pass_weight(m))});
                 }
             }
             // z chunk by z chunk, then in row bands, x fastest: blocks that run
@@ -1247,13 +1315,43 @@ struct Handle : Base {
         std::vector<double> cost;
         for (const Blk& k : tab) cost.push_back(k.cost);
         int run[16];
-        cfg.pgrid = xcd_cut(cost, run);
-        ptab.assign(2 * (size_t)cfg.pgrid, make_int4(-1, 0, 0, 0));
+        const int grid = xcd_cut(cost, run);
+        out.assign(2 * (size_t)grid, make_int4(-1, 0, 0, 0));
         for (int x = 0; x < 8; ++x)
             for (int n = 0; n < run[8 + x]; ++n) {
-                ptab[2 * ((size_t)n * 8 + x)] = tab[(size_t)run[x] + n].a;
-                ptab[2 * ((size_t)n * 8 + x) + 1] = tab[(size_t)run[x] + n].b;
+                out[2 * ((size_t)n * 8 + x)] = tab[(size_t)run[x] + n].a;
+                out[2 * ((size_t)n * 8 + x) + 1] = tab[(size_t)run[x] + n].b;
             }
+        return grid;
+    }
+
+    // The single-pass adjoint's block and tile shape, by the bytes of one
+    // adjoint set's fields as the forward's.  Measured per step (us, gradient
+    // included):         256 threads  512 threads   512 threads   512 threads
+    //                    24 groups    34 groups     67 groups     110 groups
+    //   101^3 f64, 53 MB       52          60            68            67
+    //   160^3 f32, 98 MB      113         102           100           110
+    //   212^3 f32, 242 MB     242         238           213           253
+    //   256 x 256 x 280 f32   440         392           432           431    (periodic x)
+    //   280^3 f32, 542 MB     972         919           917           932
+    // and at 536^3 f32, 4.0 GB, 2226 in chunks of 10 planes, 2508 of 48; 134
+    // groups 3570.  It is the faster adjoint at every size measured (24^3 to
+    // 536^3, both precisions; the split pair 1.05 to 5 times longer).
+    void plan_adj_pass() {
+        cfg.napass = cfg.ant = cfg.agrid = 0;
+        aptab.clear();
+        double bytes = 0;
+        bool perx = false;
+        for (int q = 0; q < ndom; ++q) {
+            if (!dd[q].apass) continue;
+            cfg.napass++;
+            bytes += 6.0 * (double)dh[q].nfield * sizeof(T);
+            perx |= dd[q].per[0] != 0;
+        }
+        if (!cfg.napass) return;
+        const int shape = bytes < 90e6 ? 0 : bytes < 120e6 ? 1 : 2;
+        cfg.ant = shape == 0 ? 256 : 512;
+        cfg.agrid = list_blocks<true>(cfg.ant, shape == 0 ? 24 : perx ? 34 : 67, shape == 0 ? 16 : 10, shape > 1, true, aptab);
     }
 
     // scalar (non-pointer) fields of the device descriptor
@@ -1340,6 +1438,7 @@ struct Handle : Base {
                 h.gelems *= (size_t)(s.grad_hi[a] - s.grad_lo[a]);
             }
             h.gncomp = d.tens ? 6 : (d.eps_diag ? 3 : 1);
+            d.apass = d.pass;
         }
         d.rev = opt.reversible && s.grad ? 1 : 0;
         h.rec_step = 0;
@@ -1765,9 +1864,13 @@ struct Handle : Base {
     int launch_adjoint_passes() {
         hipStream_t cs[kAdjClasses1];
         for (int q = 0; q < kAdjClasses1; ++q) cs[q] = st;
+        if (cfg.napass) {
+            launch_adj_pass<T>(cfg, d_doms, ap, ap ^ 1, st);
+            launch_adj_grad<T>(cfg, d_doms, ap, ap ^ 1, cur, st);
+        }
         launch_adj<T>(cfg, d_doms, ap, ap ^ 1, cur, st, 0, cs);
         for (int q = 0; q < ndom; ++q) {
-            if (!dd[q].grad) continue;
+            if (!dd[q].grad || dd[q].apass) continue;
             const bool per = dd[q].per[0] || dd[q].per[1];
             if (dd[q].tens) {
                 launch_tens_adj<T>(d_doms, q, dd[q].n, ap, ap ^ 1, cur, per, st);

@@ -25,6 +25,16 @@ struct MonDev {
     double* fout;                     // flux: F(w) [nf]
 };
 
+// Monitors whose cotangents one launch adds to the adjoint state, no two of
+// them to the same node and component (bs: first block of each, filled by
+// the launch)
+constexpr int kSeedMax = 16;
+struct SeedBatch {
+    int n;
+    int bs[kSeedMax + 1];
+    MonDev m[kSeedMax];
+};
+
 // One stepping launch over all domains: kernel 1 = split, 2 = fused; rows =
 // register-blocked rows per wave of the fused kernels; kz = z chunk.
 // Split: bs = device prefix sums of blocks per domain (ndom + 1 entries).
@@ -130,7 +140,7 @@ void launch_dft(const MonDev& m, int n0, int count, hipStream_t s, const int* td
 template <typename T>
 void launch_probe(const void* doms, const MonDev& m, int cs, int n, hipStream_t s, const int* tdev = nullptr);
 template <typename T>
-void launch_seed(const void* doms, const MonDev& m, int as_, int n, hipStream_t s);
+void launch_seed(const void* doms, SeedBatch& sb, int as_, int n, hipStream_t s);
 
 // reversible mode: record the interface of the current set cs into record
 // slot `slot` (maxcnt: the largest face of any domain); one backward step

@@ -1836,15 +1836,49 @@ struct Handle : Base {
         return check("step_forward");
     }
 
+    // whether two monitors' seeds meet in a node and component
+    static bool seeds_meet(const MonDev& a, const MonDev& b) {
+        if (a.dom != b.dom) return false;
+        auto box = [](const MonDev& m, int r[4]) {
+            r[0] = m.kind ? m.i0 : m.pi;
+            r[1] = m.kind ? m.i1 : m.pi + 1;
+            r[2] = m.kind ? m.j0 : m.pj;
+            r[3] = m.kind ? m.j1 : m.pj + 1;
+        };
+        int p[4], q[4];
+        box(a, p);
+        box(b, q);
+        if (p[0] >= q[1] || q[0] >= p[1] || p[2] >= q[3] || q[2] >= p[3]) return false;
+        // flux: Ex, Ey at its plane, Hx, Hy at its plane and the one below
+        auto adds = [](const MonDev& m, int c, int k) {
+            if (m.kind != 1) return c == m.comp && k == m.k;
+            return c < 2 ? k == m.k : (c == 3 || c == 4) && (k == m.k || k + 1 == m.k);
+        };
+        for (int c = 0; c < 6; ++c)
+            for (int k = a.k - 1; k <= a.k; ++k)
+                if (adds(a, c, k) && adds(b, c, k)) return true;
+        return false;
+    }
+
+    // the cotangents of step n, in the monitors' order where they meet
     int seed(int n) {
+        SeedBatch sb;
+        sb.n = 0;
         for (auto& h : dh) {
             if (!h.desc.grad) continue;
             for (auto& mh : h.mons) {
                 if (!mh.cot_set) continue;
                 if (mh.dev.kind == 0 && (n - 1 >= opt.max_steps || n < 1)) continue;
-                launch_seed<T>(d_doms, mh.dev, ap, n, st);
+                bool meets = sb.n == kSeedMax;
+                for (int e = 0; e < sb.n && !meets; ++e) meets = seeds_meet(sb.m[e], mh.dev);
+                if (meets) {
+                    launch_seed<T>(d_doms, sb, ap, n, st);
+                    sb.n = 0;
+                }
+                sb.m[sb.n++] = mh.dev;
             }
         }
+        if (sb.n) launch_seed<T>(d_doms, sb, ap, n, st);
         return check("seed");
     }
 

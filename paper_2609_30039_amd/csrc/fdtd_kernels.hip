@@ -2127,43 +2127,55 @@ __global__ void k_sample(const DomDev<T>* __restrict__ doms, MonDev m, int cs, i
 
 // Accumulate `count` buffered samples taken at steps n0 .. n0+count-1 into the
 // FP64 spectra acc[f][comp][pt] += x * exp(-i w t), t = n (E) or n + 1/2 (H).
-// grid.y = frequency; the block's twiddles sit in LDS.
+// One launch for all monitors: a block takes 256 points of one component of
+// one monitor at kDftFreqs frequencies, their factors in LDS, so a sample is
+// read once per kDftFreqs frequencies.  What bounds it is the chain of a
+// thread's samples.  Per ring of samples, a launch per monitor with a thread per
+// frequency over all components before: 32^3 f64 two of 18 us -> one of 15;
+// 148^3 f32 two of 25 -> one of 20; batch of 12 domains 24 of 29 -> two of 36.
+constexpr int kDftFreqs = 4;
+
 template <typename T>
-__global__ void k_dft(MonDev m, int n0, int count, const int* __restrict__ tdev) {
-    __shared__ double tw[2][2][kMaxDftBlock];   // [E|H][cos|sin][sample]
-    if (tdev) n0 += *tdev;
-    int f = blockIdx.y;
-    double w = m.omega[f];
-    for (int s = threadIdx.x; s < count; s += blockDim.x) {
-        double te = (double)(n0 + s), th = te + 0.5;
-        double sn, cs;
-        sincos(w * te, &sn, &cs);
-        tw[0][0][s] = cs;
-        tw[0][1][s] = sn;
-        sincos(w * th, &sn, &cs);
-        tw[1][0][s] = cs;
-        tw[1][1][s] = sn;
+__global__ void __launch_bounds__(256) k_dft(DftBatch db, const int* __restrict__ tdev) {
+    __shared__ double2 tw[kDftFreqs][kMaxDftBlock];   // (cos, sin)
+    const int e = find_domain(db.bs, db.n, blockIdx.x);
+    const MonDev& m = db.m[e];
+    const int n0 = db.n0[e] + (tdev ? *tdev : 0), count = db.count[e];
+    const int npts = (m.i1 - m.i0) * (m.j1 - m.j0), per = (npts + 255) / 256;
+    const int b = blockIdx.x - db.bs[e], pc = b / per, cq = pc % m.ncomp, f0 = pc / m.ncomp * kDftFreqs;
+    const int q = (b - pc * per) * 256 + threadIdx.x;
+    const int ish = (m.kind == 1) ? (cq >= 2) : (m.comp >= 3);
+    for (int x = threadIdx.x; x < kDftFreqs * count; x += 256) {
+        const int f = x / count, s = x - f * count;
+        const double t = (double)(n0 + s) + (ish ? 0.5 : 0.0);
+        double sn = 0, cs = 0;
+        if (f0 + f < m.nf) sincos(m.omega[f0 + f] * t, &sn, &cs);
+        tw[f][s] = make_double2(cs, sn);
     }
     __syncthreads();
-    int npts = (m.i1 - m.i0) * (m.j1 - m.j0);
-    int q = blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= npts) return;
-    const T* buf = (const T*)m.samples;
-    for (int cq = 0; cq < m.ncomp; ++cq) {
-        int ish = (m.kind == 1) ? (cq >= 2) : (m.comp >= 3);
-        // ring component(s) of spectrum component cq: flux <Hx>, <Hy> average planes k and k-1
-        const int r0 = (m.kind == 1 && cq >= 2) ? 2 * cq - 2 : cq;
-        double re = 0, im = 0;
-        for (int s = 0; s < count; ++s) {
-            const T* b = buf + (long long)s * m.rcomp * npts + q;
-            const T v = (m.kind == 1 && cq >= 2) ? T(0.5) * (b[r0 * npts] + b[(r0 + 1) * npts]) : b[r0 * npts];
-            double x = (double)v;
-            re = fma(x, tw[ish][0][s], re);
-            im = fma(-x, tw[ish][1][s], im);
+    // ring component(s) of spectrum component cq: flux <Hx>, <Hy> average planes k and k-1
+    const bool avg = m.kind == 1 && cq >= 2;
+    const long long st = (long long)m.rcomp * npts;
+    const FDTD_GLOBAL T* p = gp((const T*)m.samples) + (long long)(avg ? 2 * cq - 2 : cq) * npts + q;
+    double re[kDftFreqs] = {}, im[kDftFreqs] = {};
+#pragma unroll 8
+    for (int s = 0; s < count; ++s) {
+        const T v = avg ? T(0.5) * (p[s * st] + p[s * st + npts]) : p[s * st];
+        const double x = (double)v;
+#pragma unroll
+        for (int f = 0; f < kDftFreqs; ++f) {
+            const double2 w = tw[f][s];
+            re[f] = fma(x, w.x, re[f]);
+            im[f] = fma(-x, w.y, im[f]);
         }
-        double* a = m.acc + (((long long)f * m.ncomp + cq) * npts + q) * 2;
-        a[0] += re;
-        a[1] += im;
+    }
+#pragma unroll
+    for (int f = 0; f < kDftFreqs; ++f) {
+        if (f0 + f >= m.nf) break;
+        double* a = m.acc + (((long long)(f0 + f) * m.ncomp + cq) * npts + q) * 2;
+        a[0] += re[f];
+        a[1] += im[f];
     }
 }
 
@@ -2752,9 +2764,14 @@ void launch_sample(const void* doms, const MonDev& m, int cs, int slot, hipStrea
 }
 
 template <typename T>
-void launch_dft(const MonDev& m, int n0, int count, hipStream_t s, const int* tdev) {
-    int npts = (m.i1 - m.i0) * (m.j1 - m.j0);
-    hipLaunchKernelGGL(k_dft<T>, dim3((npts + 255) / 256, m.nf), dim3(256), 0, s, m, n0, count, tdev);
+void launch_dft(DftBatch& db, hipStream_t s, const int* tdev) {
+    db.bs[0] = 0;
+    for (int e = 0; e < db.n; ++e) {
+        const MonDev& m = db.m[e];
+        const int npts = (m.i1 - m.i0) * (m.j1 - m.j0);
+        db.bs[e + 1] = db.bs[e] + (npts + 255) / 256 * m.ncomp * ((m.nf + kDftFreqs - 1) / kDftFreqs);
+    }
+    if (db.bs[db.n]) hipLaunchKernelGGL(k_dft<T>, dim3(db.bs[db.n]), dim3(256), 0, s, db, tdev);
 }
 
 template <typename T>
@@ -2899,7 +2916,7 @@ int split_blocks(int nx, int ny, int nz, int kz, int w) {
     template void launch_fwd<T>(const LaunchCfg&, const void*, int, int, int, hipStream_t, const int*, int, bool); \
     template void launch_adj<T>(const LaunchCfg&, const void*, int, int, int, hipStream_t, int, const hipStream_t*); \
     template void launch_sample<T>(const void*, const MonDev&, int, int, hipStream_t);        \
-    template void launch_dft<T>(const MonDev&, int, int, hipStream_t, const int*);            \
+    template void launch_dft<T>(DftBatch&, hipStream_t, const int*);                          \
     template void launch_probe<T>(const void*, const MonDev&, int, int, hipStream_t, const int*); \
     template void launch_seed<T>(const void*, SeedBatch&, int, int, hipStream_t);                \
     template void launch_rev_record<T>(const void*, int, int, int, int, hipStream_t);          \

@@ -35,6 +35,15 @@ struct SeedBatch {
     MonDev m[kSeedMax];
 };
 
+// Plane monitors whose buffered samples (count from step n0 on) one launch sums
+constexpr int kDftMax = 16;
+struct DftBatch {
+    int n;
+    int bs[kDftMax + 1];
+    int n0[kDftMax], count[kDftMax];
+    MonDev m[kDftMax];
+};
+
 // One stepping launch over all domains: kernel 1 = split, 2 = fused; rows =
 // register-blocked rows per wave of the fused kernels; kz = z chunk.
 // Split: bs = device prefix sums of blocks per domain (ndom + 1 entries).
@@ -136,7 +145,7 @@ void launch_per_adj_h(const void* doms, int dom, const int n[3], int rs, int ws,
 template <typename T>
 void launch_sample(const void* doms, const MonDev& m, int cs, int slot, hipStream_t s);
 template <typename T>
-void launch_dft(const MonDev& m, int n0, int count, hipStream_t s, const int* tdev = nullptr);
+void launch_dft(DftBatch& db, hipStream_t s, const int* tdev = nullptr);
 template <typename T>
 void launch_probe(const void* doms, const MonDev& m, int cs, int n, hipStream_t s, const int* tdev = nullptr);
 template <typename T>

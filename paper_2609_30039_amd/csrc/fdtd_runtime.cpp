@@ -1648,10 +1648,25 @@ struct Handle : Base {
     }
 
     // ------------------------------------------------------------ stepping
-    void flush(MonHost& mh) {
-        if (mh.dev.kind == 0 || mh.pending == 0) return;
-        launch_dft<T>(mh.dev, mh.n0, mh.pending, st);
-        mh.pending = 0;
+    // Sums the buffered samples of every plane monitor holding at least `from`
+    // of them.  (Together: a launch for all, and the monitors stay at one slot.)
+    void flush(int from = 1) {
+        DftBatch db;
+        db.n = 0;
+        auto go = [&] {
+            if (db.n) launch_dft<T>(db, st);
+            db.n = 0;
+        };
+        for (auto& h : dh)
+            for (auto& mh : h.mons) {
+                if (mh.dev.kind == 0 || mh.pending < from) continue;
+                if (db.n == kDftMax) go();
+                db.m[db.n] = mh.dev;
+                db.n0[db.n] = mh.n0;
+                db.count[db.n++] = mh.pending;
+                mh.pending = 0;
+            }
+        go();
     }
 
     // Ring slot in which the split H kernel can sample every plane monitor
@@ -1673,6 +1688,7 @@ struct Handle : Base {
     // (their samples were written by the H kernel when sampled is set).
     void record(bool sampled) {
         int n = t;   // the current set holds E^n, H^{n+1/2}
+        bool full = false;
         for (auto& h : dh)
             for (auto& mh : h.mons) {
                 if (mh.dev.kind == 0) {
@@ -1682,8 +1698,9 @@ struct Handle : Base {
                 }
                 if (mh.pending == 0) mh.n0 = n;
                 if (!sampled) launch_sample<T>(d_doms, mh.dev, cur, mh.pending, st);
-                if (++mh.pending == dft_block) flush(mh);
+                full |= ++mh.pending == dft_block;
             }
+        if (full) flush(dft_block);
     }
 
     void ev_mark() {
@@ -1734,10 +1751,22 @@ struct Handle : Base {
                 for (auto& mh : h.mons)
                     if (mh.dev.kind == 0 && !dd[mh.dev.dom].pass) launch_probe<T>(d_doms, mh.dev, rset, s, cst, d_tstep);
         }
-        if (rec)
+        if (rec) {
+            DftBatch db;
+            db.n = 0;
             for (auto& h : dh)
-                for (auto& mh : h.mons)
-                    if (mh.dev.kind != 0) launch_dft<T>(mh.dev, 1, G, cst, d_tstep);
+                for (auto& mh : h.mons) {
+                    if (mh.dev.kind == 0) continue;
+                    db.m[db.n] = mh.dev;
+                    db.n0[db.n] = 1;
+                    db.count[db.n++] = G;
+                    if (db.n == kDftMax) {
+                        launch_dft<T>(db, cst, d_tstep);
+                        db.n = 0;
+                    }
+                }
+            if (db.n) launch_dft<T>(db, cst, d_tstep);
+        }
         launch_graph_advance(d_tstep, G, rset != 0, cst);
         GraphEx ge{key, nullptr, nullptr};
         if (hipStreamEndCapture(cst, &ge.g) != hipSuccess || !ge.g)
@@ -2069,7 +2098,7 @@ struct Handle : Base {
             return check("monitor reset");
         }
         if (op == FDTD_MON_GET || op == FDTD_MON_FLUX) {
-            flush(mh);
+            flush();
             if (m.kind == 0) {
                 if (op != FDTD_MON_GET) return fail(FDTD_E_INVALID, "flux of a probe");
                 size_t nb = std::min(bytes / 8, ms) * 8;
@@ -2780,9 +2809,9 @@ struct Streamer : StreamBase {
         if ((rc = xfer(hd, src_bank, true, o, e, c0, c1, st))) return rc;
         if ((rc = hd.step_forward(n, record ? FDTD_RECORD : FDTD_REPLAY))) return fail(rc, hd.err);
         if ((rc = xfer(hd, dst_bank, false, o, e, c0, c1, st))) return rc;
+        if (record) hd.flush();
         for (size_t li = 0; record && li < lm.size(); ++li) {
             MonHost& mh = hd.dh[0].mons[li];
-            hd.flush(mh);
             GMon& m = gm[lm[li]];
             launch_add_f64(m.acc, m.kind ? mh.dev.acc : mh.dev.trace, m.elems, st);
         }

@@ -1,0 +1,44 @@
+"""Tensor adjoint nodes at the edges of their numbering: rows and planes that
+fill no whole block, slabs on one side of an axis only and none at all, so that
+the nodes clear of slabs and walls and the others meet in one wave; the gradient
+against the oracle's transposed sweep."""
+import numpy as np
+import pytest
+
+from paper_2609_30039_amd import workloads as W
+from tests.gpu_util import gpu_gradient_store_all, oracle_gradient, rel
+
+pytestmark = pytest.mark.gpu
+
+
+def _cot(mi, m, sp):
+    return 2.0 * np.asarray(sp)
+
+
+# the bars of the tensor gradient elsewhere: FP64 round-off, FP32 by its rounding order
+@pytest.mark.parametrize("dtype,tol", [("f64", 1e-11), ("f32", 2e-5)])
+@pytest.mark.parametrize("shape,pml", [
+    ((7, 6, 9), (0,) * 6),
+    ((17, 15, 13), (3, 0, 0, 4, 2, 0)),
+    ((33, 9, 12), (0, 5, 3, 0, 0, 4)),
+    ((20, 26, 11), (3,) * 6),
+])
+def test_tensor_gradient_at_odd_shapes(shape, pml, dtype, tol):
+    nx, ny, nz = shape
+    rng = np.random.Generator(np.random.PCG64(nx))
+    lo = tuple(pml[2 * a] for a in range(3))
+    hi = tuple(shape[a] - pml[2 * a + 1] for a in range(3))
+    b = tuple(hi[a] - lo[a] for a in (2, 1, 0))
+    n = 24
+    spec = W.DomainSpec(
+        shape=shape, courant=W.courant_3d(), pml=pml, eps_kind="tensor", eps_box=(lo, hi),
+        eps=W.random_spd_tensors(rng, b[0] * b[1] * b[2]).reshape((6,) + b), n_steps=n, grad_box=(lo, hi),
+        sources=[W.SourceSpec("point", 2, (nx // 2, ny // 2, nz // 2), W.gaussian_sine(n, 0.5, 4.0, 6.0))],
+        monitors=[W.MonitorSpec("patch_z", comp=0, pos=(0, 0, nz // 2 + 1), rect=(1, nx, 1, ny), omega_dt=W.freq_grid(3)),
+                  W.MonitorSpec("patch_z", comp=4, pos=(0, 0, nz // 2), rect=(0, nx, 0, ny), omega_dt=W.freq_grid(2))])
+    sim, g, _ = gpu_gradient_store_all(spec, dtype, _cot)
+    sim.close()
+    _, ref = oracle_gradient(spec, _cot)
+    ref = ref[:, lo[2]:hi[2], lo[1]:hi[1], lo[0]:hi[0]]
+    assert np.abs(ref).max() > 0 and g.shape == ref.shape
+    assert rel(g, ref) < tol

@@ -2396,7 +2396,7 @@ struct Streamer : StreamBase {
         o.n_ckpt = n_ckpt;
         o.dtype = so.dtype;
         o.max_steps = so.max_steps;
-        o.kernel = FDTD_KERNEL_SPLIT;
+        o.kernel = FDTD_KERNEL_AUTO;
         o.tile_rows = so.tile_rows;
         o.tile_kz = so.tile_kz;
         o.stream = so.stream;
@@ -2461,14 +2461,14 @@ struct Streamer : StreamBase {
 
     // device address of the slab handle's copy of global array q and the
     // first global plane it holds (nullptr: the slab does not hold it)
-    // (cot: the cotangent copy, in the handle's adjoint set aset)
+    // (of the current forward set; cot: the cotangent copy, in adjoint set aset)
     T* slab_array(Handle<T>& hd, const GArr& q, int o, int e, int& sz0, int& sz1, bool cot = false,
                   int aset = 0) const {
         const DomDev<T>& d = hd.dd[0];
         sz0 = std::max(q.z0, o);
         sz1 = std::min(q.z1, e);
         if (sz1 <= sz0) return nullptr;
-        const long long so = cot ? (long long)aset * d.as : 0;
+        const long long so = cot ? (long long)aset * d.as : (long long)hd.cur * d.fs;
         switch (q.kind) {
             case 0:
                 return (cot ? (q.c < 3 ? d.Ea[q.c] : d.Ha[q.c - 3]) : (q.c < 3 ? d.E[q.c] : d.H[q.c - 3])) + so;
@@ -2476,12 +2476,12 @@ struct Streamer : StreamBase {
             case 2: {
                 if (q.a == 2 && ((q.side == 0 && o != 0) || (q.side == 1 && e != nz))) return nullptr;
                 if (cot) return (q.kind == 1 ? d.psiEa[q.a][q.side][q.r] : d.psiHa[q.a][q.side][q.r]) + so;
-                return q.kind == 1 ? d.psiE[q.a][q.side][q.r] : d.psiH[q.a][q.side][q.r];
+                return (q.kind == 1 ? d.psiE[q.a][q.side][q.r] : d.psiH[q.a][q.side][q.r]) + so;
             }
             default: {
                 if (!d.has_lor) return nullptr;
                 const long long lbox = d.lbox;
-                return (cot ? d.lora[q.w][q.c] + so : d.lor[q.w][q.c]) + (long long)q.p * lbox;
+                return (cot ? d.lora[q.w][q.c] : d.lor[q.w][q.c]) + so + (long long)q.p * lbox;
             }
         }
     }

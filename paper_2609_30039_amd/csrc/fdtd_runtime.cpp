@@ -214,31 +214,43 @@ static void sym3_inverse(const double m[6], double out[6]) {
 // into the caller's pageable buffer by the runtime costs a call per row of a
 // pitched field (a 148^3 solve with its six fields read: 165 ms, 11 ms with
 // this class) and runs a large contiguous array at 9 GB/s, page faults of a
-// fresh buffer included (a 402 MB gradient: ~40 ms, ~10 ms). A kernel writes rows
+// fresh buffer included (a 422 MB gradient: ~40 ms, 11 ms). A kernel writes rows
 // back to back into a ring of pinned slots over the bus while up to four host
 // threads move the filled slots out, so the faults are taken in parallel. The
-// ring grows to what a call can use (16 slots of 1 MiB at most), belongs to
-// its handle and is freed with it; without pinned memory the caller falls
-// back to the runtime's copy.
+// pinned memory grows to the largest call, 32 MiB at most, belongs to its
+// handle and is freed with it; without it the caller falls back to the
+// runtime's copy.
 class Readback {
-    static constexpr size_t kSlot = 1 << 20;
-    static constexpr int kRing = 16;
+    // A call takes eight slots of an eighth of it, so that short ones overlap
+    // too (6 fields of 6 MB and spectra: 6.8 ms so, 7.5 in slots of 4 MiB) and
+    // long ones make few launches (422 MB: 11.3 ms in slots of 4 MiB, 13.9 in 16
+    // of 1 MiB, whose launches of 25 us leave gaps on the bus).
+    static constexpr int kRing = 8;
+    static constexpr size_t kMinSlot = 256 << 10, kMaxPin = 32 << 20;
     static constexpr int kThreads = 4;
     static constexpr size_t kThreaded = 4 << 20;   // bytes from which helper threads pay for their start (~0.1 ms)
-    char* pin[kRing] = {};
+    char* pin = nullptr;
+    size_t cap = 0;
     hipEvent_t ev[kRing] = {};
-    int have = 0;
+    int nev = 0;
 
-    void grow(int want) {
-        while (have < want) {
-            if (hipHostMalloc((void**)&pin[have], kSlot, 0) != hipSuccess) break;
-            if (hipEventCreateWithFlags(&ev[have], hipEventDisableTiming) != hipSuccess) {
-                (void)hipHostFree(pin[have]);
-                break;
+    bool grow(size_t bytes) {
+        for (; nev < kRing; ++nev)
+            if (hipEventCreateWithFlags(&ev[nev], hipEventDisableTiming) != hipSuccess) {
+                (void)hipGetLastError();
+                return false;
             }
-            ++have;
+        const size_t want = std::min(kMaxPin, std::max(kRing * kMinSlot, (bytes + (1 << 20) - 1) >> 20 << 20));
+        if (want <= cap) return true;
+        char* p = nullptr;
+        if (hipHostMalloc((void**)&p, want, 0) != hipSuccess) {
+            (void)hipGetLastError();
+            return cap > 0;
         }
-        if (have < want) (void)hipGetLastError();
+        if (pin) (void)hipHostFree(pin);   // (nothing in flight between calls)
+        pin = p;
+        cap = want;
+        return true;
     }
 
 public:
@@ -247,29 +259,29 @@ public:
     Readback& operator=(const Readback&) = delete;
 
     void release() {
-        for (int i = 0; i < have; ++i) {
-            (void)hipEventDestroy(ev[i]);
-            (void)hipHostFree(pin[i]);
-        }
-        have = 0;
+        for (int i = 0; i < nev; ++i) (void)hipEventDestroy(ev[i]);
+        if (pin) (void)hipHostFree(pin);
+        pin = nullptr;
+        cap = 0;
+        nev = 0;
     }
 
     // rows x n elements of es bytes (pitch elements apart) at src -> out.
     // 0: done, 1: no pinned slot (nothing queued), -1: a device error
     int run(const void* src, size_t es, size_t n, size_t pitch, size_t rows, char* out, hipStream_t st) {
-        const size_t total = n * rows, per = kSlot / es;
+        const size_t total = n * rows;
         if (!total) return 0;
-        const size_t nchunk = (total + per - 1) / per;
-        grow((int)std::min<size_t>(nchunk, kRing));
-        const size_t ring = (size_t)have;
-        if (!ring) return 1;
+        if (!grow(total * es)) return 1;
+        // (whole cache lines, at most an eighth of the pinned memory)
+        const size_t slot = std::min(cap / kRing, std::max(kMinSlot, total * es / kRing + 1)) / 256 * 256;
+        const size_t per = slot / es, nchunk = (total + per - 1) / per, ring = kRing;
         std::mutex mu;
         std::condition_variable work, freed;
         size_t ready = 0, next = 0;           // chunks landed; chunks taken by a copier
         bool stop = false, busy[kRing] = {};
         std::vector<std::thread> team;
         auto move = [&](size_t k) {
-            std::memcpy(out + k * kSlot, pin[k % ring], std::min(per, total - k * per) * es);
+            std::memcpy(out + k * slot, pin + k % ring * slot, std::min(per, total - k * per) * es);
         };
         auto copier = [&] {
             std::unique_lock<std::mutex> lk(mu);
@@ -284,7 +296,7 @@ public:
                 freed.notify_one();
             }
         };
-        if (total * es >= kThreaded && ring > 1) {
+        if (total * es >= kThreaded) {
             try {
                 team.reserve(kThreads);
                 for (int i = 0; i < kThreads; ++i) team.emplace_back(copier);
@@ -303,7 +315,7 @@ public:
                     busy[b] = true;
                 }
                 const size_t e0 = queued * per;
-                launch_rows_out(src, es, n, pitch, e0, std::min(per, total - e0), pin[b], st);
+                launch_rows_out(src, es, n, pitch, e0, std::min(per, total - e0), pin + b * slot, st);
                 if (hipGetLastError() != hipSuccess || hipEventRecord(ev[b], st) != hipSuccess) {
                     ok = false;
                     break;

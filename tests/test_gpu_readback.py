@@ -1,8 +1,8 @@
 """Readback of fields, spectra and gradients (fdtd_get_field, fdtd_monitor_dft,
 fdtd_get_grad) through the pinned ring: the bytes are those of the device
 arrays, at row lengths that leave every remainder of a 16-byte store, at sizes
-below one 1 MiB slot, of whole slots, past the 16-slot ring, and at and above
-the 4 MiB from which helper threads copy."""
+below one slot, of whole slots, around the eight slots of the ring, and at and
+above the 4 MiB from which helper threads copy."""
 import numpy as np
 import pytest
 

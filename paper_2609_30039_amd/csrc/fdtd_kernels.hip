@@ -2352,18 +2352,17 @@ __global__ void __launch_bounds__(256) k_rev_record(const DomDev<T>* __restrict_
     if (!d.rev) return;
     const long long so = (long long)cs * d.fs;
     T* rec = d.rec + (long long)slot * d.rec_stride;
-    for (int f = 0; f < 6; ++f) {
-        if (d.rface[f] < 0) continue;
-        const int a = f % 3;
-        const long long cnt = d.rfcnt[a];
-        for (long long q = (long long)blockIdx.x * 256 + threadIdx.x; q < cnt; q += (long long)gridDim.x * 256) {
-            int i, j, k;
-            rev_face_cell(d, f, q, i, j, k);
-            const long long fi = fidx(d, i, j, k) + so;
-            T* const* src = f >= 3 ? d.E : d.H;
-            gp(rec)[d.rface[f] + q] = gp(src[(a + 1) % 3])[fi];
-            gp(rec)[d.rface[f] + cnt + q] = gp(src[(a + 2) % 3])[fi];
-        }
+    const int f = blockIdx.z;
+    if (d.rface[f] < 0) return;
+    const int a = f % 3;
+    const long long cnt = d.rfcnt[a];
+    for (long long q = (long long)blockIdx.x * 256 + threadIdx.x; q < cnt; q += (long long)gridDim.x * 256) {
+        int i, j, k;
+        rev_face_cell(d, f, q, i, j, k);
+        const long long fi = fidx(d, i, j, k) + so;
+        T* const* src = f >= 3 ? d.E : d.H;
+        gp(rec)[d.rface[f] + q] = gp(src[(a + 1) % 3])[fi];
+        gp(rec)[d.rface[f] + cnt + q] = gp(src[(a + 2) % 3])[fi];
     }
 }
 
@@ -2401,30 +2400,45 @@ __device__ __forceinline__ T rev_h_down(const DomDev<T>& d, const T* rec, const 
     return rev_rec(d, rec, a, c == (a + 1) % 3 ? 0 : 1, y[0], y[1], y[2]);
 }
 
+// A thread's cell of R, one each: numbered along the rows of a plane, plane
+// after plane, with 32-bit divisions, each XCD a contiguous run (160^3: 31 and
+// 33 us a launch with 64-bit ones dealt round-robin, now 31 and 28; the record
+// of the faces, one after the other before, 10 and now 6).
+template <typename T>
+__device__ __forceinline__ bool rev_cell(const DomDev<T>& d, int& i, int& j, int& k) {
+    const int rx = d.rhi[0] - d.rlo[0], ry = d.rhi[1] - d.rlo[1], per = (rx * ry + 255) / 256;
+    if (per == 0) return false;
+    const int b = xcd_remap(blockIdx.x, gridDim.x);
+    k = b / per;
+    const int r = (b - k * per) * 256 + threadIdx.x;
+    j = r / rx;
+    i = d.rlo[0] + r - j * rx;
+    j += d.rlo[1];
+    k += d.rlo[2];
+    return r < rx * ry && k < d.rhi[2];
+}
+
 // H^{m-1/2} over R from E^m (set rs) and H^{m+1/2} (set rs) into set ws,
-// with the interface E^m of record slot m; grid y = domain, x over R's cells
+// with the interface E^m of record slot m; grid y = domain, x over R's cells (rev_cell)
 template <typename T>
 __global__ void __launch_bounds__(256) k_rev_h(const DomDev<T>* __restrict__ doms, int rs, int ws, int slot) {
     const DomDev<T>& d = doms[blockIdx.y];
     if (!d.rev) return;
-    const int rx = d.rhi[0] - d.rlo[0], ry = d.rhi[1] - d.rlo[1], rz = d.rhi[2] - d.rlo[2];
-    const long long ncell = (long long)rx * ry * rz;
+    int i, j, k;
+    if (!rev_cell(d, i, j, k)) return;
     const T* rec = d.rec + (long long)slot * d.rec_stride;
     const long long so = (long long)rs * d.fs, wo = (long long)ws * d.fs;
     const FDTD_GLOBAL T* e[3] = {gp(d.E[0] + so), gp(d.E[1] + so), gp(d.E[2] + so)};
     const T S = d.S;
-    for (long long q = (long long)blockIdx.x * 256 + threadIdx.x; q < ncell; q += (long long)gridDim.x * 256) {
-        const int i = d.rlo[0] + (int)(q % rx), j = d.rlo[1] + (int)((q / rx) % ry), k = d.rlo[2] + (int)(q / ((long long)rx * ry));
-        const long long f = fidx(d, i, j, k);
-        const T ex = e[0][f], ey = e[1][f], ez = e[2][f];
-        // Hx: d+_y Ez - d+_z Ey ; Hy: d+_z Ex - d+_x Ez ; Hz: d+_x Ey - d+_y Ex
-        const T Dx0 = rev_e_up(d, rec, e[2], f, 2, 1, i, j, k) - ez, Dx1 = rev_e_up(d, rec, e[1], f, 1, 2, i, j, k) - ey;
-        const T Dy0 = rev_e_up(d, rec, e[0], f, 0, 2, i, j, k) - ex, Dy1 = rev_e_up(d, rec, e[2], f, 2, 0, i, j, k) - ez;
-        const T Dz0 = rev_e_up(d, rec, e[1], f, 1, 0, i, j, k) - ey, Dz1 = rev_e_up(d, rec, e[0], f, 0, 1, i, j, k) - ex;
-        gp(d.H[0] + wo)[f] = fma(S, Dx0 - Dx1, gp(d.H[0] + so)[f]);
-        gp(d.H[1] + wo)[f] = fma(S, Dy0 - Dy1, gp(d.H[1] + so)[f]);
-        gp(d.H[2] + wo)[f] = fma(S, Dz0 - Dz1, gp(d.H[2] + so)[f]);
-    }
+    const long long f = fidx(d, i, j, k);
+    const T ex = e[0][f], ey = e[1][f], ez = e[2][f];
+    // Hx: d+_y Ez - d+_z Ey ; Hy: d+_z Ex - d+_x Ez ; Hz: d+_x Ey - d+_y Ex
+    const T Dx0 = rev_e_up(d, rec, e[2], f, 2, 1, i, j, k) - ez, Dx1 = rev_e_up(d, rec, e[1], f, 1, 2, i, j, k) - ey;
+    const T Dy0 = rev_e_up(d, rec, e[0], f, 0, 2, i, j, k) - ex, Dy1 = rev_e_up(d, rec, e[2], f, 2, 0, i, j, k) - ez;
+    const T Dz0 = rev_e_up(d, rec, e[1], f, 1, 0, i, j, k) - ey, Dz1 = rev_e_up(d, rec, e[0], f, 0, 1, i, j, k) - ex;
+    gp(d.H[0] + wo)[f] = fma(S, Dx0 - Dx1, gp(d.H[0] + so)[f]);
+    gp(d.H[1] + wo)[f] = fma(S, Dy0 - Dy1, gp(d.H[1] + so)[f]);
+    gp(d.H[2] + wo)[f] = fma(S, Dz0 - Dz1, gp(d.H[2] + so)[f]);
 }
 
 // E^{m-1} over R from E^m (set rs) and H^{m-1/2} (set ws, written by k_rev_h)
@@ -2434,34 +2448,31 @@ template <typename T>
 __global__ void __launch_bounds__(256) k_rev_e(const DomDev<T>* __restrict__ doms, int rs, int ws, int slot, int t) {
     const DomDev<T>& d = doms[blockIdx.y];
     if (!d.rev) return;
-    const int rx = d.rhi[0] - d.rlo[0], ry = d.rhi[1] - d.rlo[1], rz = d.rhi[2] - d.rlo[2];
-    const long long ncell = (long long)rx * ry * rz;
+    int i, j, k;
+    if (!rev_cell(d, i, j, k)) return;
     const T* rec = d.rec + (long long)slot * d.rec_stride;
     const long long so = (long long)rs * d.fs, wo = (long long)ws * d.fs;
     const FDTD_GLOBAL T* h[3] = {gp(d.H[0] + wo), gp(d.H[1] + wo), gp(d.H[2] + wo)};
     const T S = d.S;
-    for (long long q = (long long)blockIdx.x * 256 + threadIdx.x; q < ncell; q += (long long)gridDim.x * 256) {
-        const int i = d.rlo[0] + (int)(q % rx), j = d.rlo[1] + (int)((q / rx) % ry), k = d.rlo[2] + (int)(q / ((long long)rx * ry));
-        const long long f = fidx(d, i, j, k);
-        const T hx = h[0][f], hy = h[1][f], hz = h[2][f];
-        // Ex: d-_y Hz - d-_z Hy ; Ey: d-_z Hx - d-_x Hz ; Ez: d-_x Hy - d-_y Hx
-        const T Dx0 = hz - rev_h_down(d, rec, h[2], f, 2, 1, i, j, k), Dx1 = hy - rev_h_down(d, rec, h[1], f, 1, 2, i, j, k);
-        const T Dy0 = hx - rev_h_down(d, rec, h[0], f, 0, 2, i, j, k), Dy1 = hz - rev_h_down(d, rec, h[2], f, 2, 0, i, j, k);
-        const T Dz0 = hy - rev_h_down(d, rec, h[1], f, 1, 0, i, j, k), Dz1 = hx - rev_h_down(d, rec, h[0], f, 0, 1, i, j, k);
-        const T D[3] = {Dx0 - Dx1, Dy0 - Dy1, Dz0 - Dz1};
-        for (int c = 0; c < 3; ++c) {
-            if (e_masked(c, i, j, k)) {
-                gp(d.E[c] + wo)[f] = T(0);
-                continue;
-            }
-            T v = gp(d.E[c] + so)[f];
-            for (int q2 = 0; q2 < d.nsrc; ++q2) {
-                const SrcDev<T>& sr = d.src[q2];
-                if (sr.comp == c && t < sr.nwave && k == sr.k && (sr.kind == 1 || (i == sr.i && j == sr.j)))
-                    v -= gp(sr.wave)[t];
-            }
-            gp(d.E[c] + wo)[f] = fma(-S * epsinv_at(d, c, i, j, k), D[c], v);
+    const long long f = fidx(d, i, j, k);
+    const T hx = h[0][f], hy = h[1][f], hz = h[2][f];
+    // Ex: d-_y Hz - d-_z Hy ; Ey: d-_z Hx - d-_x Hz ; Ez: d-_x Hy - d-_y Hx
+    const T Dx0 = hz - rev_h_down(d, rec, h[2], f, 2, 1, i, j, k), Dx1 = hy - rev_h_down(d, rec, h[1], f, 1, 2, i, j, k);
+    const T Dy0 = hx - rev_h_down(d, rec, h[0], f, 0, 2, i, j, k), Dy1 = hz - rev_h_down(d, rec, h[2], f, 2, 0, i, j, k);
+    const T Dz0 = hy - rev_h_down(d, rec, h[1], f, 1, 0, i, j, k), Dz1 = hx - rev_h_down(d, rec, h[0], f, 0, 1, i, j, k);
+    const T D[3] = {Dx0 - Dx1, Dy0 - Dy1, Dz0 - Dz1};
+    for (int c = 0; c < 3; ++c) {
+        if (e_masked(c, i, j, k)) {
+            gp(d.E[c] + wo)[f] = T(0);
+            continue;
         }
+        T v = gp(d.E[c] + so)[f];
+        for (int q2 = 0; q2 < d.nsrc; ++q2) {
+            const SrcDev<T>& sr = d.src[q2];
+            if (sr.comp == c && t < sr.nwave && k == sr.k && (sr.kind == 1 || (i == sr.i && j == sr.j)))
+                v -= gp(sr.wave)[t];
+        }
+        gp(d.E[c] + wo)[f] = fma(-S * epsinv_at(d, c, i, j, k), D[c], v);
     }
 }
 
@@ -2873,12 +2884,12 @@ int flux_scratch(double** out) {
 
 template <typename T>
 void launch_rev_record(const void* doms, int ndom, int cs, int slot, int maxcnt, hipStream_t s) {
-    k_rev_record<T><<<dim3(blocks_1d(maxcnt, 256, 4096), ndom), 256, 0, s>>>((const DomDev<T>*)doms, cs, slot);
+    k_rev_record<T><<<dim3(blocks_1d(maxcnt, 256, 4096), ndom, 6), 256, 0, s>>>((const DomDev<T>*)doms, cs, slot);
 }
 
 template <typename T>
-void launch_rev_step(const void* doms, int ndom, int rs, int ws, int m, long long maxcells, hipStream_t s) {
-    const dim3 g(blocks_1d(maxcells, 256, 16384), ndom);
+void launch_rev_step(const void* doms, int ndom, int rs, int ws, int m, int maxblk, hipStream_t s) {
+    const dim3 g(maxblk > 0 ? maxblk : 1, ndom);
     k_rev_h<T><<<g, 256, 0, s>>>((const DomDev<T>*)doms, rs, ws, m);
     k_rev_e<T><<<g, 256, 0, s>>>((const DomDev<T>*)doms, rs, ws, m - 1, m - 1);
 }
@@ -2920,7 +2931,7 @@ int split_blocks(int nx, int ny, int nz, int kz, int w) {
     template void launch_probe<T>(const void*, const MonDev&, int, int, hipStream_t, const int*); \
     template void launch_seed<T>(const void*, SeedBatch&, int, int, hipStream_t);                \
     template void launch_rev_record<T>(const void*, int, int, int, int, hipStream_t);          \
-    template void launch_rev_step<T>(const void*, int, int, int, int, long long, hipStream_t);        \
+    template void launch_rev_step<T>(const void*, int, int, int, int, int, hipStream_t);              \
     template void launch_energy<T>(const void*, int, int, double*, double*, hipStream_t);
 FDTD_INSTANTIATE(float)
 FDTD_INSTANTIATE(double)

@@ -1,10 +1,11 @@
 // fdtd_node_adj.h -- pieces shared by the per-node adjoint passes of tensor
 // media and Bloch-periodic domains (internal).
 //
-// These passes give each thread one (i, j) column of kNodeKz planes of a
-// domain, 64 x-columns by 4 rows per 256-thread block, and march it in z:
+// The periodic passes give each thread one (i, j) column of kNodeKz planes of
+// a domain, 64 x-columns by 4 rows per 256-thread block, and march it in z:
 // the z neighbour a node reads is the previous (or next) plane of the same
-// thread, carried in registers, so a plane's operands are fetched once.
+// thread, carried in registers, so a plane's operands are fetched once.  The
+// tensor passes gather node by node.
 #pragma once
 #include "fdtd_dev.h"
 

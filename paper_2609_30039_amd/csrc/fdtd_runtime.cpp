@@ -402,8 +402,7 @@ struct Handle : Base {
     std::vector<GraphEx> graphs;
     // reversible mode: record slots [rec_lo, rec_hi] hold the interface of the
     // current trajectory (-1: none)
-    int rec_lo = -1, rec_hi = -1, rev_maxcnt = 0;
-    long long rev_maxcells = 0;
+    int rec_lo = -1, rec_hi = -1, rev_maxcnt = 0, rev_maxblk = 0;
     Readback readback;
     // kernel timing
     bool timing_on = false;
@@ -952,8 +951,8 @@ struct Handle : Base {
             for (int q = 0; q < n; ++q) {
                 rev_maxcnt = std::max(rev_maxcnt, std::max(dd[q].rfcnt[0], std::max(dd[q].rfcnt[1], dd[q].rfcnt[2])));
                 if (dd[q].rev)
-                    rev_maxcells = std::max(rev_maxcells, (long long)(dd[q].rhi[0] - dd[q].rlo[0]) *
-                                                              (dd[q].rhi[1] - dd[q].rlo[1]) * (dd[q].rhi[2] - dd[q].rlo[2]));
+                    rev_maxblk = std::max(rev_maxblk, ((dd[q].rhi[0] - dd[q].rlo[0]) * (dd[q].rhi[1] - dd[q].rlo[1]) + 255) / 256 *
+                                                          (dd[q].rhi[2] - dd[q].rlo[2]));
             }
         }
         nsets = 2 + (bf16 ? 0 : o->n_ckpt);
@@ -1826,7 +1825,7 @@ struct Handle : Base {
             const bool working = cur == wset[0] || cur == wset[1];
             const int ws = working ? cur : write_set();
             if (timing_on) ev_mark();
-            launch_rev_step<T>(d_doms, ndom, cur, ws, t, rev_maxcells, st);
+            launch_rev_step<T>(d_doms, ndom, cur, ws, t, rev_maxblk, st);
             if (timing_on) ev_mark();
             cur = ws;
             --t;

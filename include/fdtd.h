@@ -96,10 +96,11 @@ enum { FDTD_MON_GET = 0, FDTD_MON_FLUX = 1, FDTD_MON_SET_COTANGENT = 2, FDTD_MON
 /* kernel family.  SPLIT: one E launch and one H launch per step, updating the
    state in place; FUSED: one pass per step over tiles, writing the other state
    set; ONEPASS: one z-marching launch per step that advances E and H together,
-   writing the other state set, on the domains it admits (scalar or diagonal
-   permittivity; a periodic x axis with an even number of FP32 cells), the
-   split kernels on the others; AUTO: without a launch shape (tile_rows,
-   tile_kz) ONEPASS or SPLIT by the size of the state, with one SPLIT.  Results
+   writing the other state set, and one that transposes both in the adjoint,
+   on the domains it admits (scalar or diagonal permittivity; a periodic x axis
+   with an even number of FP32 cells), the split kernels on the others; AUTO:
+   without a launch shape (tile_rows, tile_kz) ONEPASS, its forward by the size
+   of the state, with one SPLIT.  Results
    are bitwise identical; the speed depends on the geometry (the package's
    autotuner picks per workload).  ONEPASS takes tile_rows 4 or 8 (for the
    domains on the split kernels), tile_kz planes per block (0: by size) and no

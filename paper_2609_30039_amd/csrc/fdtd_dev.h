@@ -263,11 +263,14 @@ __device__ __forceinline__ int find_domain(const int* __restrict__ bs, int ndom,
 // In-kernel sampling (slot >= 0): a thread whose column lies in a plane
 // monitor's rectangle writes, on the monitor plane, E^{n+1} and the new H,
 // and on the plane below (flux) the new Hx, Hy, into the ring slot.
-template <typename T>
-__device__ __forceinline__ void sample_node(const DomDev<T>& d, int slot, int i, int j, int k, T ex, T ey, T ez,
+// (D: the descriptor, in whichever address space the caller reads it: through the
+// constant one the monitor tests are scalar loads instead of a chain of vector
+// ones; recorded steps of k_pass 9.2 -> 8.0 us on a 32^3 f64 box, 2799 -> 2729 on 536^3)
+template <typename T, typename D>
+__device__ __forceinline__ void sample_node(const D& d, int slot, int i, int j, int k, T ex, T ey, T ez,
                                             T hx, T hy, T hz) {
     for (int q = 0; q < d.nsmp; ++q) {
-        const SmpDev& m = d.smp[q];
+        const auto& m = d.smp[q];
         if (i < m.i0 || i >= m.i1 || j < m.j0 || j >= m.j1) continue;
         const bool on = k == m.k, below = m.kind == 1 && k + 1 == m.k;
         if (!on && !below) continue;

@@ -97,7 +97,6 @@ __device__ __forceinline__ T slab_term(bool in, T b, T c, T ki, T psi, T D, T& p
 template <typename T, int V>
 struct PassCtx {
     Const<DomDev<T>>* d;
-    const DomDev<T>* dg;         // the same, for the sampling code it shares with the split kernels
     int tid, row, col, i, j, k0, k1, nz;
     int il, ir, id, iu;          // threads of the neighbouring groups: left, right, row below, row above
     bool wl, wr, wd, wu;         // the neighbour past a wall: left, right, row below, row above
@@ -478,7 +477,7 @@ __device__ __forceinline__ void pass_march(const PassCtx<T, V>& c, PassLds<T, V,
         if (first && c.smp_planes >> (kp - c.k0) & 1 && c.own)
             for (int v = 0; v < V; ++v)
                 if (!(v > 0 && c.tail))
-                    sample_node(*c.dg, c.slot, c.i + v, c.j, kp, Ek[0].v[v], Ek[1].v[v], Ek[2].v[v], Hw[0].v[v], Hw[1].v[v],
+                    sample_node<T>(d, c.slot, c.i + v, c.j, kp, Ek[0].v[v], Ek[1].v[v], Ek[2].v[v], Hw[0].v[v], Hw[1].v[v],
                                 Hw[2].v[v]);
         if (first && c.prb_planes >> (kp - c.k0) & 1 && c.own)
             for (int q = 0; q < d.nprb; ++q) {
@@ -516,7 +515,6 @@ __device__ __attribute__((noinline, noreturn)) void pass_tile(const DomDev<T>* d
     Const<DomDev<T>>& d = as_const(doms)[dom];
     PassCtx<T, V> c;
     c.d = &d;
-    c.dg = doms + dom;
     const int nx = d.n[0], ny = d.n[1], nz = d.n[2];
     const bool perx = d.per[0], pery = d.per[1];
     c.nz = nz;

@@ -190,8 +190,9 @@ typedef struct {
     int32_t dft_block;             /* time samples buffered before a DFT flush (0: default) */
     int32_t graph_chunk;           /* steps per captured hipGraph (0: no graph) */
     int32_t tile_rows;             /* fused kernels: rows per wave, 2 | 4 | 8 (0: 2); split kernels:
-                                      rows per 256-thread block, 4 (64 columns; 0 = 4) or 8 (32) */
-    int32_t tile_kz;               /* z planes per block (0: default) */
+                                      rows per 256-thread block, 4 (64 columns) or 8 (32); 0 = 4
+                                      with a tile_kz, else 8 */
+    int32_t tile_kz;               /* z planes per block (0: by family and size) */
     void *stream;                  /* hipStream_t; NULL = default stream */
     double mem_budget_bytes;       /* refuse with FDTD_E_NOMEM above this (0: device free memory) */
     int32_t reversible;            /* 1: reversible mode (see fdtd_step_reverse); admissible only when

@@ -2756,11 +2756,11 @@ void launch_adj(const LaunchCfg& c, const void* doms, int rs, int ws, int fsr, h
     if (c.kernel == 1) {
         // ta1: [general tiles (na1g)][the other classes]
         if (pass == 0 && c.na1g)
-            hipLaunchKernelGGL(k_adj_ht_full<T>, dim3(c.na1g), dim3(256), 0, s, dd, c.ta1, c.kz, rs, ws, fsr);
+            hipLaunchKernelGGL(k_adj_ht_full<T>, dim3(c.na1g), dim3(256), 0, s, dd, c.ta1, c.akz, rs, ws, fsr);
         if (pass == 0 && c.na1 > c.na1g)
-            hipLaunchKernelGGL(k_adj_ht<T>, dim3(c.na1 - c.na1g), dim3(256), 0, s, dd, c.ta1 + c.na1g, c.kz, rs, ws,
+            hipLaunchKernelGGL(k_adj_ht<T>, dim3(c.na1 - c.na1g), dim3(256), 0, s, dd, c.ta1 + c.na1g, c.akz, rs, ws,
                                fsr);
-        if (pass == 1 && c.na2) hipLaunchKernelGGL(k_adj_et<T>, dim3(c.na2), dim3(256), 0, s, dd, c.ta2, c.kz, rs, ws);
+        if (pass == 1 && c.na2) hipLaunchKernelGGL(k_adj_et<T>, dim3(c.na2), dim3(256), 0, s, dd, c.ta2, c.akz, rs, ws);
         return;
     }
     if (pass != 0) return;

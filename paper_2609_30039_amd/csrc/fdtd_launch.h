@@ -52,6 +52,7 @@ constexpr int kAdjClasses1 = 7, kAdjClasses2 = 6;
 
 struct LaunchCfg {
     int kernel, rows, kz, nblk, ndom;
+    int akz;                   // z chunk of the split adjoint
     int sw;                    // split forward: block width in columns (64 or 32; 256 / sw rows)
     const int* bs;             // split blocks per domain (prefix sums)
     const int* xr;             // split: per-XCD runs of column blocks, 8 starts then 8 lengths

@@ -567,7 +567,7 @@ struct Handle : Base {
     // on this: a class only handles the slabs its mask names.
     void build_adjoint_tiles() {
         for (auto& l : atiles) l.clear();
-        const int kz = cfg.kz;
+        const int kz = cfg.akz;
         for (int q = 0; q < ndom; ++q) {
             const fdtd_domain_desc& s = dh[q].desc;
             if (!s.grad || dd[q].apass) continue;
@@ -917,11 +917,10 @@ struct Handle : Base {
         if (o->tile_kz < 0) return fail(FDTD_E_INVALID, "tile_kz");
         cfg.kernel = o->kernel == FDTD_KERNEL_FUSED ? 2 : 1;
         cfg.rows = o->tile_rows ? o->tile_rows : 2;
-        // split family: tile_rows = rows per block, 4 (64 columns) or 8 (32 columns)
+        // split family: tile_rows = rows per block, 4 (64 columns) or 8 (32 columns); 0: 4 with a tile_kz, else 8
         if (cfg.kernel == 1 && o->tile_rows != 0 && o->tile_rows != 4 && o->tile_rows != 8)
             return fail(FDTD_E_INVALID, "split kernels take tile_rows 4 or 8");
-        cfg.sw = (cfg.kernel == 1 && o->tile_rows == 8) ? 32 : 64;
-        cfg.kz = o->tile_kz ? o->tile_kz : (cfg.kernel == 1 ? 8 : 16);
+        cfg.sw = cfg.kernel == 1 && (o->tile_rows == 8 || (!o->tile_rows && !o->tile_kz)) ? 32 : 64;
         cfg.ndom = n;
         dh.resize(n);
         dd.assign(n, DomDev<T>{});
@@ -930,6 +929,26 @@ struct Handle : Base {
             if (rc) return rc;
             init_scalars(q);
         }
+        // Split shape without an explicit one (us per step): 32 columns leave fewer
+        // lanes idle at a row's end, and short chunks make enough blocks.
+        //                         64 x 4, 8   32 x 8, 3   32 x 8, 8 planes
+        //   48^3 f32 tensor              49          25          52
+        //   148^3 f32 tensor            121          96         108
+        //   200^3 f32 tensor            343         275         290
+        //   200^3 f64 tensor            638         538         557
+        //   180^3 f32                   109          95         104
+        //   400^3 f32 tensor           2050        1916        1980
+        //   536^3 f32 tensor           4482        4484        4396
+        // The adjoint's tiles keep 8 planes where scalar media use them; the
+        // tensor adjoint's (its H-node pass) gain as the forward does.
+        double fbytes = 0;
+        bool tens = false;
+        for (int q = 0; q < n; ++q) {
+            fbytes += 6.0 * (double)dh[q].nfield * sizeof(T);
+            tens |= dd[q].tens != 0;
+        }
+        cfg.kz = o->tile_kz ? o->tile_kz : cfg.kernel != 1 ? 16 : fbytes < 2.5e9 ? 3 : 8;
+        cfg.akz = o->tile_kz || tens ? cfg.kz : 8;
         if (o->reversible) {
             // Section 3.2: the reversible mode needs a lossless, nondispersive box
             // between the absorbing slabs that holds the gradient box with the H
@@ -958,16 +977,17 @@ struct Handle : Base {
         nsets = 2 + (bf16 ? 0 : o->n_ckpt);
         if (o->kernel == FDTD_KERNEL_AUTO) {
             // In-place stepping keeps one working set in the last-level cache
-            // (256 MB) where the single pass needs two.  With fields of 120 to
+            // (256 MB) where the single pass needs two.  With fields of 90 to
             // 236 MB one set stays and two do not, and the split pair is the
-            // faster (us per step, split against single pass): 140^3 f64 111
-            // against 119, 160^3 f64 139 and 155, 180^3 f32 109 and 130, 190^3
-            // f32 115 and 146; outside it 130^3 f64 116 and 100, 170^3 f64 228
-            // and 195, 160^3 f32 99 and 80, 212^3 f32 240 and 190.
+            // faster (us per step, split against single pass): 160^3 f32 70
+            // against 81, 175^3 f32 90 and 131, 205^3 f32 145 and 178, 125^3 f64
+            // 75 and 93, 140^3 f64 88 and 119, 164^3 f64 184 and 197; outside it
+            // 140^3 f32 59 and 52, 110^3 f64 63 and 52, 212^3 f32 187 and 187,
+            // 220^3 f32 213 and 197, 170^3 f64 202 and 194.
             double b = 0;
             for (int q = 0; q < n; ++q)
                 if (dd[q].pass) b += 6.0 * (double)dh[q].nfield * sizeof(T);
-            if (b >= 120e6 && b < 236e6)
+            if (b >= 90e6 && b < 236e6)
                 for (auto& d : dd) d.pass = 0;
         }
         plan_pass();

@@ -1,11 +1,12 @@
 """Tensor adjoint nodes at the edges of their numbering: rows and planes that
 fill no whole block, slabs on one side of an axis only and none at all, so that
 the nodes clear of slabs and walls and the others meet in one wave; the gradient
-against the oracle's transposed sweep."""
+against the oracle's transposed sweep, and the forward across launch shapes."""
 import numpy as np
 import pytest
 
 from paper_2609_30039_amd import workloads as W
+from paper_2609_30039_amd.sim import Simulation
 from tests.gpu_util import gpu_gradient_store_all, oracle_gradient, rel
 
 pytestmark = pytest.mark.gpu
@@ -42,3 +43,24 @@ def test_tensor_gradient_at_odd_shapes(shape, pml, dtype, tol):
     ref = ref[:, lo[2]:hi[2], lo[1]:hi[1], lo[0]:hi[0]]
     assert np.abs(ref).max() > 0 and g.shape == ref.shape
     assert rel(g, ref) < tol
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("shape", [(7, 6, 9), (65, 33, 10), (96, 17, 4)])
+def test_default_launch_shape_equals_explicit_ones_bitwise(shape, dtype):
+    nx, ny, nz = shape
+    rng = np.random.Generator(np.random.PCG64(ny))
+    spec = W.DomainSpec(
+        shape=shape, courant=W.courant_3d(), pml=(0, 2, 0, 0, 0, 0), eps_kind="tensor", eps_box=((0, 0, 0), (nx - 2, ny, nz)),
+        eps=W.random_spd_tensors(rng, nz * ny * (nx - 2)).reshape((6, nz, ny, nx - 2)), n_steps=8,
+        sources=[W.SourceSpec("point", 2, (nx // 2, ny // 2, nz // 2), W.gaussian_sine(8, 0.5, 3.0, 2.0))])
+    got = []
+    for kw in (dict(), dict(kernel="split"), dict(tile_rows=4, tile_kz=8), dict(tile_rows=8, tile_kz=3), dict(tile_kz=2)):
+        sim = Simulation(spec, dtype=dtype, **kw)
+        sim.step(8)
+        got.append([sim.field(c) for c in range(6)])
+        sim.close()
+    assert max(np.abs(x).max() for x in got[0]) > 0
+    for other in got[1:]:
+        for x, y in zip(got[0], other):
+            assert np.array_equal(x, y)

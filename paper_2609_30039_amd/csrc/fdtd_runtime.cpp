@@ -1194,11 +1194,13 @@ struct Handle : Base {
         const bool hl = d.per[0] || t.x > 0, hb = d.per[1] || t.z > 0, hr = d.per[0] || t.y < nq, ht = d.per[1] || t.w < d.n[1];
         const int lo[3] = {std::max((t.x - hl) * V, 0), std::max(t.z - hb, 0), std::max(k0 - 1, 0)};
         const int hi[3] = {std::min((t.y + hr) * V, d.n[0]) - 1, std::min(t.w + ht, d.n[1]) - 1, std::min(k1, d.n[2] - 1)};
+        // the high halo of a tile that ends at a seam lies on the axis' first nodes
+        const int wrap[3] = {d.per[0] && t.y == nq ? V : 0, d.per[1] && t.w == d.n[1] ? 1 : 0, 0};
         int m = 0;
         bool lor = d.has_lor != 0;
         for (int a = 0; a < 3; ++a) {
             if (lo[a] < d.L[a][0] || hi[a] >= d.n[a] - d.L[a][1]) m |= 1 << a;
-            if (hi[a] < d.llo[a] || lo[a] >= d.lhi[a]) lor = false;
+            if ((hi[a] < d.llo[a] || lo[a] >= d.lhi[a]) && d.llo[a] >= wrap[a]) lor = false;
         }
         if ((d.per[0] && (t.x == 0 || t.y == nq)) || (d.per[1] && (t.z == 0 || t.w == d.n[1]))) m |= kAdjPer;
         if (lor) return m ? (int)kAdjAll : (int)kAdjLor;

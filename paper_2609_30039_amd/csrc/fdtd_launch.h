@@ -116,7 +116,7 @@ enum AdjMask { kAdjPer = 8, kAdjLor = 16, kAdjAll = 31 };
 constexpr int kAdjMaxGroups = 136;    // column groups of its tiles, halo included
 constexpr int kPassMaxGroups = 272;   // column groups of a tile, halo included (coefficient tables in LDS)
 constexpr int kPassMaxRows = 112;     // rows of a tile, halo included
-constexpr int kPassMaxPlanes = 64;    // planes of a tile (one bit each in the event masks)
+constexpr int kPassMaxPlanes = 63;    // planes of a tile (with the one above, one bit each in the event masks)
 template <typename T> constexpr int kPassGroup = sizeof(T) == 4 ? 2 : 1;   // x nodes per thread: 8 bytes
 // the single-pass adjoint over the domains that take it: sets rs -> ws
 template <typename T>

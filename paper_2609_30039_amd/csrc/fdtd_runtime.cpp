@@ -1240,12 +1240,9 @@ struct Handle : Base {
             const int to = std::min(std::max(cutp[q], 0), nz), from = zb.back();
             if (to <= from || (to - from < 3 && to < nz && from > 0)) continue;
             const int len = std::max(2, (int)(kz / weight(mask(from, to)) + 0.5));
-            const int n = std::max(1, (to - from + len / 2) / len);
+            const int n = std::max({1, (to - from + len / 2) / len, (to - from + kPassMaxPlanes - 1) / kPassMaxPlanes});
             for (int c = 1; c <= n; ++c) zb.push_back(from + (int)((long long)(to - from) * c / n));
         }
-        if (zb.back() < nz) zb.push_back(nz);
-        for (size_t c = 0; c + 1 < zb.size(); ++c)   // the kernel's limit
-            if (zb[c + 1] - zb[c] > kPassMaxPlanes) zb.insert(zb.begin() + c + 1, zb[c] + kPassMaxPlanes);
     }
 
     // cost of a plane of a tile against a lean one

@@ -2,8 +2,8 @@
 // included as source, handles are planned without a device (size_only), and
 // the block tables and the admission are compared with a node-by-node reading
 // of what each block computes.  The kernels' launches come from the library.
-//   plan_driver masks   what a block's variant must handle, tile limits, one
-//                       owner per node
+//   plan_driver masks   what a block's variant must handle, tile limits, planes
+//                       in the event masks, one owner per node
 #include "../../paper_2609_30039_amd/csrc/fdtd_runtime.cpp"
 
 #include <random>
@@ -102,6 +102,8 @@ void check_blocks(const Handle<T>& h, const Case& c) {
         if (wt * rt > nt || rt > kPassMaxRows || wt > (ADJ ? kAdjMaxGroups : kPassMaxGroups) || b.w - b.z > kPassMaxPlanes ||
             a.w <= a.z || b.y <= b.x || b.w <= b.z)
             bad("tile out of its limits", a, b);
+        if (!ADJ && b.w - b.z + 1 > 64)   // the march's planes, halo included, in the event masks
+            bad("more planes than the event masks have bits", a, b);
         const int have = ADJ ? adj_variant(a.y) : fwd_variant(a.y), seam = ADJ ? (int)kAdjPer : (int)kPassMix,
                   disp = ADJ ? (int)kAdjLor : (int)kPassMix;
         int need = 0;

@@ -452,6 +452,13 @@ struct Handle : Base {
 
     char* set_ptr(int q) { return fbase + (size_t)q * fstride; }
 
+    // elements of one absorber memory array (0: no slab)
+    static size_t psi_elems(const DomDev<T>& d, int a, int side) {
+        const size_t L = (size_t)d.L[a][side];
+        if (!L) return 0;
+        return a == 0 ? (size_t)d.lxp[side] * d.n[1] * d.n[2] : L * (size_t)d.ppx * (a == 1 ? d.n[2] : d.n[1]);
+    }
+
     size_t n_bs() const { return 3 * ((size_t)ndom + 1) + 16; }
 
     // ------------------------------------------------------------ tiles
@@ -764,7 +771,6 @@ struct Handle : Base {
             DomHost& h = dh[q];
             DomDev<T>& d = dd[q];
             const fdtd_domain_desc& s = h.desc;
-            const int nx = s.n[0], ny = s.n[1], nz = s.n[2];
             const bool g = s.grad != 0;
             auto fst = [&](T*& p, size_t n) {
                 F.take(p, n * ts);
@@ -790,8 +796,7 @@ struct Handle : Base {
                 for (int side = 0; side < 2; ++side) {
                     // (the single-pass kernel relies on this order: the arrays of
                     // one axis side by side, at one distance per side)
-                    size_t L = (size_t)s.pml[2 * a + side];
-                    size_t ne = !L ? 0 : a == 0 ? (size_t)d.lxp[side] * ny * nz : L * (size_t)d.ppx * (a == 1 ? nz : ny);
+                    const size_t ne = psi_elems(d, a, side);
                     for (int r = 0; r < 2; ++r) {
                         if (!ne) continue;
                         fst(d.psiE[a][side][r], ne);
@@ -1141,11 +1146,10 @@ struct Handle : Base {
         if (s.n[0] - s.pml[0] - s.pml[1] < V && s.pml[0] && s.pml[1]) return false;
         const double lim = 2147483648.0, ts = sizeof(T);
         if (ts * d.pitch * s.n[1] >= lim) return false;
-        for (int a = 0; a < 3; ++a) {
-            const double row = a == 0 ? (double)s.n[1] * s.n[2] : (double)d.ppx * (a == 1 ? s.n[2] : s.n[1]);
-            double span = 0;
-            for (int side = 0; side < 2; ++side) span += 4.0 * (s.pml[2 * a + side] * row * ts + 256.0);
-            if (span >= lim) return false;
+        for (int a = 0; a < 3; ++a) {   // the four arrays of each side, as layout places them
+            size_t span = 0;
+            for (int side = 0; side < 2; ++side) span += 4 * align256(psi_elems(d, a, side) * sizeof(T));
+            if ((double)span >= lim) return false;
         }
         const double ebox = ts * (s.eps_hi[0] - s.eps_lo[0] + 64.0) * (s.eps_hi[1] - s.eps_lo[1]);
         return ebox < lim;

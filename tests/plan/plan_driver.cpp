@@ -4,6 +4,8 @@
 // of what each block computes.  The kernels' launches come from the library.
 //   plan_driver masks   what a block's variant must handle, tile limits, planes
 //                       in the event masks, one owner per node
+//   plan_driver spans   absorber memories, planes and eps rows of admitted
+//                       domains within the 31-bit offsets of their descriptors
 #include "../../paper_2609_30039_amd/csrc/fdtd_runtime.cpp"
 
 #include <random>
@@ -216,11 +218,86 @@ void masks() {
     if (taken < 300 && ++failures) std::printf("only %d plans took a single pass\n", taken);
 }
 
+// bytes from the first to the end of the last absorber array of an axis (the
+// kernels' psi_range), from the pointers that layout gives
+template <typename T, typename P>
+double span(const DomDev<T>& d, int a, const P& psiE, const P& psiH) {
+    double lo = 1e30, hi = 0;
+    for (int side = 0; side < 2; ++side) {
+        if (!d.L[a][side]) continue;
+        const double e0 = (double)(size_t)psiE[a][side][0], h0 = (double)(size_t)psiH[a][side][0];
+        if (h0 - e0 != (double)(size_t)psiE[a][side][1] - h0 || h0 - e0 != (double)(size_t)psiH[a][side][1] - (double)(size_t)psiE[a][side][1])
+            ++failures, std::printf("axis %d side %d: arrays not at one distance\n", a, side);
+        lo = std::min(lo, e0);
+        hi = std::max(hi, e0 + 4 * (h0 - e0));
+    }
+    return hi > lo ? hi - lo : 0;
+}
+
+template <typename T>
+int check_spans(const Case& c) {
+    Handle<T> h;
+    if (!plan(h, c)) return 0;
+    Arena ar[4];
+    for (int q = 0; q < 4; ++q) {
+        ar[q].base = (char*)0 + ((size_t)(q + 1) << 44);   // never read
+        ar[q].assign = true;
+    }
+    h.layout(ar[0], ar[1], ar[2], ar[3]);
+    const DomDev<T>& d = h.dd[0];
+    const double lim = 2147483648.0;   // an offset of it must lie outside
+    double most = (double)d.plane * sizeof(T);
+    for (int a = 0; a < 3; ++a) {
+        most = std::max(most, span(d, a, d.psiE, d.psiH));
+        if (d.grad) most = std::max(most, span(d, a, d.psiEa, d.psiHa));
+    }
+    if ((d.pass || d.apass) != (most < lim)) {
+        ++failures;
+        std::printf("%s: span %.6e, pass %d, adjoint %d\n", name(c).c_str(), most, d.pass, d.apass);
+    }
+    return 1;
+}
+
+void spans() {
+    struct S {
+        int n[3], L, dtype;
+    };
+    // odd numbers of cells of x slabs round up to pairs, by two on the high side of an odd nx
+    const S set[] = {{{101, 2500, 2500}, 10, FDTD_F32}, {{100, 3000, 3000}, 7, FDTD_F32}, {{101, 1800, 1800}, 10, FDTD_F64},
+                     {{100, 2500, 2500}, 10, FDTD_F32}, {{100, 2600, 2600}, 10, FDTD_F32}, {{41, 4000, 4000}, 1, FDTD_F32},
+                     {{2501, 81, 2500}, 40, FDTD_F32},  {{3001, 3001, 40}, 7, FDTD_F64},   {{200, 200, 200}, 11, FDTD_F64}};
+    for (const S& e : set)
+        for (int sides = 1; sides < 4; ++sides) {
+            Case c = blank(e.n[0], e.n[1], e.n[2], e.dtype, FDTD_KERNEL_ONEPASS, 0);
+            for (int a = 0; a < 3; ++a) {
+                if (sides & 1) c.d.pml[2 * a] = e.L;
+                if (sides & 2) c.d.pml[2 * a + 1] = e.L;
+            }
+            if (e.dtype == FDTD_F32) check_spans<float>(c);
+            else check_spans<double>(c);
+        }
+    // sizes a little either side of the limit
+    std::mt19937 rng(11);
+    auto pick = [&](int lo, int hi) { return std::uniform_int_distribution<int>(lo, hi)(rng); };
+    for (int q = 0; q < 60; ++q) {
+        const bool f64 = pick(0, 1);
+        const int L = pick(1, 12), M = pick(0, 12), nx = pick(L + M + 4, L + M + 60);
+        const double rows = 2147483648.0 / (4.0 * (f64 ? 8 : 4) * (L + M)) * (0.7 + 0.01 * pick(0, 35));
+        const int ny = pick(300, 3000), nz = std::max(8, (int)(rows / ny));
+        Case c = blank(nx, ny, nz, f64 ? FDTD_F64 : FDTD_F32, FDTD_KERNEL_ONEPASS, 0);
+        c.d.pml[0] = L;
+        c.d.pml[1] = M;
+        if (f64) check_spans<double>(c);
+        else check_spans<float>(c);
+    }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "masks") masks();
+    else if (what == "spans") spans();
     else return 2;
     std::printf("%s: %s\n", what.c_str(), failures ? "FAILED" : "ok");
     return failures ? 1 : 0;

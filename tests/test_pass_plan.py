@@ -35,3 +35,10 @@ def test_blocks_take_a_variant_that_covers_their_nodes(driver):
     slabs, seams and dispersive cells are in the block's variant; each node has
     one owner; tiles keep the kernels' limits."""
     _check(driver, "masks")
+
+
+def test_admitted_absorber_memories_fit_their_descriptors(driver):
+    """Domains whose absorber memories, rounded up to pairs of x nodes, reach
+    2 GiB stay off the single pass (its dropped accesses use that offset); those
+    below take it."""
+    _check(driver, "spans")

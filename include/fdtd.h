@@ -103,8 +103,7 @@ enum { FDTD_MON_GET = 0, FDTD_MON_FLUX = 1, FDTD_MON_SET_COTANGENT = 2, FDTD_MON
    of the state, with one SPLIT.  Results
    are bitwise identical; the speed depends on the geometry (the package's
    autotuner picks per workload).  ONEPASS takes tile_rows 4 or 8 (for the
-   domains on the split kernels), tile_kz planes per block (0: by size) and no
-   reversible mode. */
+   domains on the split kernels) and tile_kz planes per block (0: by size). */
 enum { FDTD_KERNEL_AUTO = 0, FDTD_KERNEL_SPLIT = 1, FDTD_KERNEL_FUSED = 2, FDTD_KERNEL_ONEPASS = 3 };
 
 #define FDTD_MAX_SOURCES 4

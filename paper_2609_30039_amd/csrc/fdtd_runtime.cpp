@@ -915,8 +915,6 @@ struct Handle : Base {
         if (bf16 && sizeof(T) != 4) return fail(FDTD_E_INVALID, "BF16 checkpoints need FP32 fields");
         if (o->n_ckpt < 0 || o->max_steps < 0) return fail(FDTD_E_INVALID, "negative n_ckpt or max_steps");
         if (o->kernel < 0 || o->kernel > 3) return fail(FDTD_E_INVALID, "kernel selector");
-        if (o->kernel == FDTD_KERNEL_ONEPASS && o->reversible)
-            return fail(FDTD_E_INVALID, "the single-pass family takes no reversible mode");
         if (o->tile_rows != 0 && o->tile_rows != 2 && o->tile_rows != 4 && o->tile_rows != 8)
             return fail(FDTD_E_INVALID, "tile_rows must be 2, 4 or 8");
         if (o->tile_kz < 0) return fail(FDTD_E_INVALID, "tile_kz");

@@ -316,8 +316,9 @@ __device__ __forceinline__ void e_lor_block(const DomDev<T>* __restrict__ doms, 
     gp(d.E[2] + wo)[f] = ez;
 }
 
-// The dispersive cells of single-pass domains with several poles: E^{n+1} and
-// histories into set ws, where the single-pass kernel reads them.  One thread
+// The dispersive cells of single-pass domains with several poles, or with the
+// largest tiles (lorpre): E^{n+1} and histories into set ws, where the
+// single-pass kernel reads them.  One thread
 // per cell and component (grid y): the pole loops are chains of loads, so
 // three times the threads of one per cell keep three times as many in flight.
 template <typename T>

@@ -978,21 +978,7 @@ struct Handle : Base {
             }
         }
         nsets = 2 + (bf16 ? 0 : o->n_ckpt);
-        if (o->kernel == FDTD_KERNEL_AUTO) {
-            // In-place stepping keeps one working set in the last-level cache
-            // (256 MB) where the single pass needs two.  With fields of 90 to
-            // 236 MB one set stays and two do not, and the split pair is the
-            // faster (us per step, split against single pass): 160^3 f32 70
-            // against 81, 175^3 f32 90 and 131, 205^3 f32 145 and 178, 125^3 f64
-            // 75 and 93, 140^3 f64 88 and 119, 164^3 f64 184 and 197; outside it
-            // 140^3 f32 59 and 52, 110^3 f64 63 and 52, 212^3 f32 187 and 187,
-            // 220^3 f32 213 and 197, 170^3 f64 202 and 194.
-            double b = 0;
-            for (int q = 0; q < n; ++q)
-                if (dd[q].pass) b += 6.0 * (double)dh[q].nfield * sizeof(T);
-            if (b >= 90e6 && b < 236e6)
-                for (auto& d : dd) d.pass = 0;
-        }
+        if (o->kernel == FDTD_KERNEL_AUTO) pick_families();
         plan_pass();
         plan_adj_pass();
         build_tiles();
@@ -1133,8 +1119,8 @@ struct Handle : Base {
     // diagonal permittivity; a periodic x axis only with whole column groups
     // (its seam joins the last group to the first); a group of columns meets
     // one x slab only; planes and absorber memories within the 31-bit offsets
-    // of their buffer descriptors.  At every size measured it is the faster
-    // forward (kernels and figures: fdtd_pass.hip).
+    // of their buffer descriptors.  (AUTO then leaves to the split kernels what
+    // they do faster: pick_families.)
     bool pass_admits(const fdtd_domain_desc& s, const DomDev<T>& d) const {
         constexpr int V = kPassGroup<T>;
         if (opt.kernel != FDTD_KERNEL_ONEPASS &&
@@ -1151,6 +1137,80 @@ struct Handle : Base {
         }
         const double ebox = ts * (s.eps_hi[0] - s.eps_lo[0] + 64.0) * (s.eps_hi[1] - s.eps_lo[1]);
         return ebox < lim;
+    }
+
+    // AUTO: whether the domains that admit the single pass take it, forward (all
+    // of them or none) and in the adjoint.  Times are us per step, split kernels
+    // against single pass.
+    //
+    // Forward.  In-place stepping keeps one working set in the last-level cache
+    // (256 MB) where the single pass needs two.  Where one set stays and two do
+    // not the split pair is the faster, by fields of 90 to 236 MB (160^3 f32 70
+    // against 81, 205^3 f32 145 and 178, 125^3 f64 75 and 93, 164^3 f64 184 and
+    // 197; outside it 140^3 f32 59 and 52, 212^3 f32 204 and 190, 220^3 f32 229
+    // and 200, 170^3 f64 215 and 198), and below that where both sets with their
+    // absorber memories and histories and the eps^-1 arrays pass 228 MB (148^3
+    // f32 66 and 78 with diagonal eps, 65 and 65 without; 132^3 f32 with 30
+    // absorbing cells 68 and 79; 150^3 f32 with one pole in 130^3 111 and 203; at
+    // 194 MB 116^3 f64 68 and 60).  Periodic domains whose histories are far
+    // beyond the cache do not (128^3 f32 with 16 poles in all of it 449 and 390).
+    // A dispersive box over a good part of a walled domain is the faster with the
+    // split kernels, whose box blocks run beside the others: from a fifth of the
+    // cells with several poles (212^3 f32, three in 192^3 592 and 661, two in
+    // 128^3 295 and 320; 170^3 f64, three in 150^3 520 and 629; in a tenth 262 and
+    // 261) but not with many in FP32 (212^3, 16 poles 1753 and 1654), and with
+    // one pole from three tenths while the fields are small (100^3 f32, 80^3 50
+    // and 63; 212^3 424 and 414).
+    //
+    // Adjoint.  The single pass is the faster but where the split kernels read
+    // the histories in whole cache lines: a periodic domain with its box over
+    // half the cells (256^3 f32, 203^3 1 pole 1002 and 1047, all of it 1076 and
+    // 1374; 180^3 f64, 158^3 3 poles 927 and 1004; smaller or with a smaller box
+    // 721 and 645 at 200^3 f32, 178^3), with many poles over a quarter (256^3
+    // f32, 171^3 16 poles 2961 and 3243), and a walled domain whose large box
+    // lies on line boundaries along x (256^3 f32, 128^3 714 and 746 with one pole,
+    // 1422 and 2234 with 16; off them at 300^3 2528 and 2445).
+    void pick_families() {
+        constexpr bool f32 = sizeof(T) == 4;
+        constexpr double ts = sizeof(T);
+        double F = 0, S = 0, E = 0, N = 0, C = 0, A = 0;   // bytes: fields, state, eps^-1; cells, dispersive cells; adjoint fields
+        int poles = 0;
+        bool per = false;
+        for (int q = 0; q < ndom; ++q) {
+            const DomDev<T>& d = dd[q];
+            if (!d.pass) continue;
+            const double f = 6.0 * (double)dh[q].nfield * ts;
+            F += f;
+            S += f;
+            for (int a = 0; a < 3; ++a)
+                for (int side = 0; side < 2; ++side) S += 4.0 * ts * (double)psi_elems(d, a, side);
+            if (d.has_lor) {
+                S += 3.0 * (1 + 2 * d.npole) * ts * (double)d.lbox;
+                C += (double)d.lbox;
+                poles = std::max(poles, d.npole);
+            }
+            E += dh[q].ncomp_eps * ts * (d.ehi[0] - d.elo[0]) * (double)(d.ehi[1] - d.elo[1]) * (d.ehi[2] - d.elo[2]);
+            N += (double)d.n[0] * d.n[1] * d.n[2];
+            per |= d.per[0] || d.per[1];
+            if (d.apass) A += f;
+        }
+        const bool small = F < 236e6;
+        const bool cache = small && (F >= 90e6 || (2 * S + E >= 228e6 && !(per && S >= 512e6)));
+        const bool disp = !per && poles > 0 &&
+                          (poles > 1 ? C >= 0.2 * N && (small || !f32 || poles < 8) : small && C >= 0.3 * N);
+        for (auto& d : dd) {
+            if (cache || disp) d.pass = 0;
+            if (!d.apass || !d.has_lor) continue;
+            const double n = (double)d.n[0] * d.n[1] * d.n[2], c = (double)d.lbox, share = c / n;
+            if (d.per[0] || d.per[1]) {
+                if (f32 ? (share >= 0.45 && A >= 300e6) || (share >= 0.28 && d.npole >= 10 && A >= 200e6)
+                        : (share >= 0.45 && A >= 250e6) || (share >= 0.6 && A >= 100e6))
+                    d.apass = 0;
+            } else if (d.llo[0] % 16 == 0 && (d.lhi[0] - d.llo[0]) % 32 == 0 && A >= 200e6 && c >= 5e5 &&
+                       c * (7 + 2.3 * d.npole) > (f32 ? 1.1 : 5.5) * n) {
+                d.apass = 0;
+            }
+        }
     }
 
     // The x-y tiles of a single-pass domain for blocks of nt threads: (q0, q1,
@@ -1373,8 +1433,8 @@ struct Handle : Base {
     //   256 x 256 x 280 f32   440         392           432           431    (periodic x)
     //   280^3 f32, 542 MB     972         919           917           932
     // and at 536^3 f32, 4.0 GB, 2226 in chunks of 10 planes, 2508 of 48; 134
-    // groups 3570.  It is the faster adjoint at every size measured (24^3 to
-    // 536^3, both precisions; the split pair 1.05 to 5 times longer).
+    // groups 3570.  The split pair takes 1.05 to 5 times longer (24^3 to 536^3,
+    // both precisions) but for some dispersive boxes (pick_families).
     void plan_adj_pass() {
         cfg.napass = cfg.ant = cfg.agrid = 0;
         aptab.clear();

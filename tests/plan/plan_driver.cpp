@@ -4,6 +4,7 @@
 // of what each block computes.  The kernels' launches come from the library.
 //   plan_driver masks   what a block's variant must handle, tile limits, planes
 //                       in the event masks, one owner per node
+//   plan_driver routes  which kernels AUTO takes, forward and adjoint
 //   plan_driver spans   absorber memories, planes and eps rows of admitted
 //                       domains within the 31-bit offsets of their descriptors
 #include "../../paper_2609_30039_amd/csrc/fdtd_runtime.cpp"
@@ -292,12 +293,73 @@ void spans() {
     }
 }
 
+// n^3 cells, pml absorbing cells on walled axes, box lo..hi per axis (hi 0:
+// none), periodic x and y; expected: single pass forward, adjoint
+void routes() {
+    struct R {
+        int n, dtype, pml, per, lo, hi, poles, fwd, adj;
+        bool diag = false;
+        int kernel = FDTD_KERNEL_AUTO, tile_kz = 0;
+    };
+    const int f = FDTD_F32, d = FDTD_F64;
+    const R set[] = {
+        {140, f, 10, 0, 0, 0, 0, 1, 1},      {160, f, 10, 0, 0, 0, 0, 0, 1},     {212, f, 10, 0, 0, 0, 0, 1, 1},
+        {148, f, 10, 0, 0, 0, 0, 1, 1},      {148, f, 10, 0, 0, 0, 0, 0, 1, true}, {132, f, 30, 0, 0, 0, 0, 0, 1},
+        {116, d, 10, 0, 0, 0, 0, 1, 1},      {125, d, 10, 0, 0, 0, 0, 0, 1},     {170, d, 10, 0, 0, 0, 0, 1, 1},
+        {150, f, 10, 0, 10, 140, 1, 0, 1},   {100, f, 10, 0, 10, 90, 1, 0, 1},   {100, f, 10, 0, 40, 72, 1, 1, 1},
+        {212, f, 10, 0, 10, 202, 1, 1, 1},   {212, f, 10, 0, 10, 202, 3, 0, 1},  {212, f, 10, 0, 10, 202, 16, 1, 1},
+        {170, d, 10, 0, 10, 160, 16, 0, 1},  {212, f, 10, 0, 42, 170, 2, 0, 1},  {212, f, 10, 0, 56, 156, 3, 1, 1},
+        {128, f, 10, 1, 0, 128, 16, 1, 1},   {128, f, 10, 1, 0, 128, 3, 0, 1},   {256, f, 10, 1, 0, 256, 3, 1, 0},
+        {200, f, 10, 1, 11, 189, 1, 0, 1},   {200, f, 10, 1, 11, 189, 16, 0, 0}, {180, d, 10, 1, 11, 169, 3, 1, 0},
+        {128, d, 10, 1, 0, 128, 1, 0, 0},    {256, f, 10, 0, 64, 192, 1, 1, 0},  {256, f, 10, 0, 96, 160, 16, 1, 1},
+        {300, f, 10, 0, 86, 214, 16, 1, 1},  {250, d, 10, 0, 64, 192, 16, 1, 0}, {250, d, 10, 0, 64, 192, 6, 1, 1},
+        {256, f, 10, 0, 64, 192, 16, 1, 1, false, FDTD_KERNEL_ONEPASS},          {256, f, 10, 0, 64, 192, 1, 0, 0, false, FDTD_KERNEL_SPLIT},
+        {140, f, 10, 0, 0, 0, 0, 0, 0, false, FDTD_KERNEL_AUTO, 8},
+    };
+    std::vector<double> eps;
+    for (const R& r : set) {
+        Case c = blank(r.n, r.n, r.n, r.dtype, r.kernel, r.tile_kz);
+        for (int q = 0; q < 6; ++q) c.d.pml[q] = r.pml;
+        if (r.per) {
+            periodic(c, 0, 1);
+            periodic(c, 1, -1);
+        }
+        const int lo[3] = {r.lo, r.lo, r.per && r.hi == r.n ? 10 : r.lo}, hi[3] = {r.hi, r.hi, r.per && r.hi == r.n ? r.n - 10 : r.hi};
+        if (r.hi) box(c, lo, hi, r.poles);
+        if (r.diag) {
+            c.d.eps_kind = FDTD_EPS_DIAG;
+            size_t cells = 1;
+            for (int a = 0; a < 3; ++a) {
+                c.d.eps_lo[a] = r.pml;
+                c.d.eps_hi[a] = r.n - r.pml;
+                cells *= (size_t)(r.n - 2 * r.pml);
+            }
+            eps.assign(3 * cells, 2.0);
+            c.d.eps = eps.data();
+        }
+        auto check = [&](auto& h) {
+            if (!plan(h, c)) return;
+            if (h.dd[0].pass == r.fwd && h.dd[0].apass == r.adj) return;
+            ++failures;
+            std::printf("%s, poles %d: forward %d, adjoint %d\n", name(c).c_str(), r.poles, h.dd[0].pass, h.dd[0].apass);
+        };
+        if (r.dtype == FDTD_F32) {
+            Handle<float> h;
+            check(h);
+        } else {
+            Handle<double> h;
+            check(h);
+        }
+    }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "masks") masks();
     else if (what == "spans") spans();
+    else if (what == "routes") routes();
     else return 2;
     std::printf("%s: %s\n", what.c_str(), failures ? "FAILED" : "ok");
     return failures ? 1 : 0;

@@ -42,3 +42,8 @@ def test_admitted_absorber_memories_fit_their_descriptors(driver):
     2 GiB stay off the single pass (its dropped accesses use that offset); those
     below take it."""
     _check(driver, "spans")
+
+
+def test_auto_takes_the_measured_route(driver):
+    """Which kernels AUTO takes on either side of each line of its rule."""
+    _check(driver, "routes")

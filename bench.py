@@ -286,7 +286,7 @@ def adjoint_536(stream):
     grads = {}
     for tag, dtype, slots, storage in (("fp32_slots", "f32", 32, None), ("bf16_slots", "f32", 32, "bf16"),
                                        ("fp64", "f64", 20, None)):
-        tile = AT.tune(spec, dtype, adjoint=True, stream=stream, log=log, steps=3, candidates=SPLIT_SHAPES[2:4])
+        tile = AT.tune(spec, dtype, adjoint=True, stream=stream, log=log, steps=3, candidates=SPLIT_SHAPES[2:4] + ONEPASS)
         kw = dict(tile)
         if storage:
             kw["ckpt_storage"] = storage
@@ -663,7 +663,7 @@ def periodic_536(stream):
     from paper_2609_30039_amd import roofline as RL
     from paper_2609_30039_amd.sim import Simulation
     spec = W.bloch_cell()
-    tile = {"kernel": "split", "tile_rows": 8, "tile_kz": 8}
+    tile = ONEPASS[0]
     sim = Simulation(spec, dtype="f32", n_ckpt=1, stream=stream, graph_chunk=BENCH_CHUNK, **tile)
     sim.step(BENCH_STEP)
     torch.cuda.synchronize()

@@ -19,7 +19,7 @@ def main(argv=None):
     ap.add_argument("--dtype", default="f32", choices=["f32", "f64"])
     ap.add_argument("--steps", type=int, default=20)
     ap.add_argument("--warmup", type=int, default=4)
-    ap.add_argument("--shape", default="auto,0,0", help="KERNEL,ROWS,KZ (kernel auto|split|fused)")
+    ap.add_argument("--shape", default="auto,0,0", help="KERNEL,ROWS,KZ (kernel auto|split|onepass|fused)")
     ap.add_argument("--adjoint", action="store_true", help="time adjoint steps instead of forward steps")
     ap.add_argument("--reverse", action="store_true",
                     help="reversible mode: after the forward steps, time as many backward steps")

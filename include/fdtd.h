@@ -96,14 +96,17 @@ enum { FDTD_MON_GET = 0, FDTD_MON_FLUX = 1, FDTD_MON_SET_COTANGENT = 2, FDTD_MON
 /* kernel family.  SPLIT: one E launch and one H launch per step, updating the
    state in place; FUSED: one pass per step over tiles, writing the other state
    set; ONEPASS: one z-marching launch per step that advances E and H together,
-   writing the other state set, and one that transposes both in the adjoint,
-   on the domains it admits (scalar or diagonal permittivity; a periodic x axis
-   with an even number of FP32 cells), the split kernels on the others; AUTO:
-   without a launch shape (tile_rows, tile_kz) ONEPASS, its forward by the size
-   of the state, with one SPLIT.  Results
-   are bitwise identical; the speed depends on the geometry (the package's
-   autotuner picks per workload).  ONEPASS takes tile_rows 4 or 8 (for the
-   domains on the split kernels) and tile_kz planes per block (0: by size). */
+   writing the other state set, and one that transposes both in the adjoint, on
+   the domains it admits, the split kernels on the others.  Admitted: scalar or
+   diagonal permittivity; on a periodic x axis an even number of FP32 cells;
+   between two absorbing x slabs at least one x node in FP64, two in FP32; a
+   plane of a field, a plane of the permittivity box and the absorber memories
+   of one axis below 2 GiB each.  AUTO: with a launch shape (tile_rows, tile_kz)
+   SPLIT; without one ONEPASS, but SPLIT forward or adjoint where the size of
+   the state or a dispersive box makes it the faster.  Results are bitwise
+   identical; the speed depends on the geometry (the package's autotuner picks
+   per workload).  ONEPASS takes tile_rows 4 or 8 (for the domains on the split
+   kernels) and tile_kz planes per block (0: by size; 63 at most are taken). */
 enum { FDTD_KERNEL_AUTO = 0, FDTD_KERNEL_SPLIT = 1, FDTD_KERNEL_FUSED = 2, FDTD_KERNEL_ONEPASS = 3 };
 
 #define FDTD_MAX_SOURCES 4
@@ -273,11 +276,18 @@ int fdtd_checkpoint_restore(fdtd_t h, int32_t slot);
    FLUX           host_buf <- double [n_freq], Re sum (Ex Hy* - Ey Hx*).
    SET_COTANGENT  host_buf -> same layout as GET: dJ/dRe X + i dJ/dIm X
                   (probes: dJ/dsample, double [max_steps]).
-   RESET          zero the spectra / trace (host_buf unused). */
+   RESET          zero the spectra / trace (host_buf unused).
+   GET and FLUX first add the buffered samples of every plane monitor of the
+   handle to its spectra: which monitors are read, and when, decides how the
+   FP64 sums of all of them are grouped, and so their last bits. */
 int fdtd_monitor_dft(fdtd_t h, int32_t domain, int32_t monitor, int32_t op, void *host_buf, size_t bytes);
 
 /* Copy one component (FDTD_EX..FDTD_HZ, + FDTD_ADJ for the cotangent) of one
-   domain to/from a host array of nx*ny*nz elements of the handle's dtype. */
+   domain to/from a host array of nx*ny*nz elements of the handle's dtype.
+   Reads of fields, spectra and gradients go through pinned host memory that the
+   handle allocates when they first need it (2 to 32 MiB by the largest, freed
+   with the handle; without it the runtime's copy), and of 4 MiB and more with up
+   to four threads of the library, which end with the call. */
 int fdtd_get_field(fdtd_t h, int32_t domain, int32_t comp, void *host_buf, size_t bytes);
 int fdtd_set_field(fdtd_t h, int32_t domain, int32_t comp, const void *host_buf, size_t bytes);
 

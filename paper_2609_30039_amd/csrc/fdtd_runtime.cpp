@@ -1347,6 +1347,8 @@ struct Handle : Base {
     // absorbing slab hold up fewer others.  Beyond it the halo rows and the
     // short row segments of small tiles cost memory traffic.  Small domains
     // take shorter z chunks until there are about 400 blocks (256 CUs).
+    // (Between 90 and 236 MB only ONEPASS comes here: AUTO steps those with the
+    // split kernels.)
     void plan_pass() {
         cfg.npass = cfg.nlorpre = cfg.pnt = cfg.pgrid = 0;
         ptab.clear();

@@ -1279,14 +1279,23 @@ struct Handle : Base {
         return m;
     }
 
-    // Dispersive tiles gather their poles one by one: a box of 96 cells in 256^3
-    // f32 took 1830 us a step of 16 poles with 0.4, 1470 so; where the box holds
-    // more than a quarter of the domain the cut at its edges costs more (96 of
-    // 144^3 f32, one pole: 210 us with 0.4, 234 by the poles; 212^3, 16 poles in
-    // nearly all of it: 3380 and 3730).
-    static double adj_weight(const DomDev<T>& d, int m) {
+    // cost of a plane of an adjoint tile against a lean one.  Dispersive tiles
+    // gather their poles one by one, and the large domains' (even), whose lean
+    // tiles wait for memory, are the dearer beside them.  us per step, 16 poles in
+    // a box of 128 cells unless said, by what a dispersive tile adds:
+    //                           0.4    0.8 + 0.3 p   0.4 + p
+    //   144^3 f32, 48               538          273       327
+    //   256^3 f32, 96              1830         1473      1384
+    //   360^3 f32                     -         3085      2814
+    //   536^3 f32                  8540         8460      7324   (split 7485)
+    //   536^3 f32, 3 poles         5674         5683      5528
+    // Where the box holds more than a quarter of the domain the cut at its edges
+    // costs more (96 of 144^3 f32, one pole: 210 with 0.4, 234 by the poles; 212^3,
+    // 16 poles in nearly all of it: 3380 and 3730).
+    static double adj_weight(const DomDev<T>& d, int m, bool even) {
         const bool most = 4.0 * (double)d.lbox > (double)d.n[0] * d.n[1] * d.n[2];
-        return pass_weight(m & 7) + (m & kAdjPer ? 0.2 : 0.0) + (m & kAdjLor ? (most ? 0.4 : 0.8 + 0.3 * d.npole) : 0.0);
+        const double lor = most ? 0.4 : even ? 0.4 + d.npole : 0.8 + 0.3 * d.npole;
+        return pass_weight(m & 7) + (m & kAdjPer ? 0.2 : 0.0) + (m & kAdjLor ? lor : 0.0);
     }
 
     // Planes of an x-y tile's blocks: bounds of chunks of about kz planes.
@@ -1304,7 +1313,7 @@ struct Handle : Base {
             return;
         }
         auto mask = [&](int k0, int k1) { return ADJ ? adj_mask(d, t, k0, k1) : pass_mask(d, t, k0, k1); };
-        auto weight = [&](int m) { return ADJ ? adj_weight(d, m) : pass_weight(m); };
+        auto weight = [&](int m) { return ADJ ? adj_weight(d, m, even) : pass_weight(m); };
         // (an adjoint tile meets a slab from the plane above it on)
         int cutp[6] = {0, d.L[2][0] + (ADJ && d.L[2][0] ? 1 : 0), d.L[2][1] ? nz - d.L[2][1] - 1 : nz, nz}, nc = 4;
         if (d.has_lor && (mask(d.llo[2], d.lhi[2]) & (ADJ ? (int)kAdjLor : (int)kPassMix))) {
@@ -1411,7 +1420,7 @@ struct Handle : Base {
                     const int m = ADJ ? adj_mask(d, t, zb[z], zb[z + 1]) : pass_mask(d, t, zb[z], zb[z + 1]);
                     tab.push_back({make_int4(q, m, t.x, t.y), make_int4(t.z, t.w, zb[z], zb[z + 1]),
                                    (double)(t.y - t.x + 1) * (t.w - t.z + 2) * (zb[z + 1] - zb[z] + 2) *
-                                       (ADJ ? adj_weight(d, m) : pass_weight(m))});
+                                       (ADJ ? adj_weight(d, m, even) : pass_weight(m))});
                 }
             }
             // z chunk by z chunk, then in row bands, x fastest: blocks that run

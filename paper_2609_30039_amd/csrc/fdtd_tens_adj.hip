@@ -117,15 +117,20 @@ __device__ __forceinline__ T fwd_curl(const DomDev<T>& d, int c, const int x[3],
 }
 
 // A thread's node.  Nodes are numbered along the rows without gaps (64-wide
-// tiles left a fifth of the lanes idle at 200 columns) and the blocks of one XCD
-// are neighbours in that order, plane after plane, so that the rows and planes
-// a node shares with its neighbours stay in its L2.
+// tiles left a fifth of the lanes idle at 200 columns) in bands of `band` blocks
+// of 256, a band plane after plane, and the blocks of one XCD are neighbours in
+// that order, so that the rows and planes a node shares with its neighbours stay
+// in its L2.  Bands of about 128 blocks keep two planes there: us
+// per adjoint step in bands of 128 and of whole planes, 200^3 f32 546 and 554,
+// 300^3 1639 and 1626, 400^3 3593 and 3668, 536^3 8373 and 8957, 536^3 f64 13374
+// and 14243; 16 blocks 8788 at 536^3 f32.
 template <typename T>
-__device__ __forceinline__ bool node_at(const DomDev<T>& d, int& i, int& j, int& k) {
-    const int area = d.n[0] * d.n[1], per = (area + 255) / 256;
+__device__ __forceinline__ bool node_at(const DomDev<T>& d, int band, int& i, int& j, int& k) {
+    const int area = d.n[0] * d.n[1];
     const int b = xcd_remap(blockIdx.x, gridDim.x);
-    k = b / per;
-    const int r = (b - k * per) * 256 + threadIdx.x;
+    const int q = b / band, s = q / d.n[2];
+    k = q - s * d.n[2];
+    const int r = (s * band + b - q * band) * 256 + threadIdx.x;
     j = r / d.n[0];
     i = r - j * d.n[0];
     return r < area;
@@ -136,10 +141,10 @@ __device__ __forceinline__ bool node_at(const DomDev<T>& d, int& i, int& j, int&
 // 200^3: 212 us as columns of 8 planes in 64 x 4 tiles through HtGather alone,
 // 174 in the numbering above, 157 with 2 planes, 139 so.
 template <typename T>
-__global__ void __launch_bounds__(256) k_tadj_ht(const DomDev<T>* __restrict__ dp, int rs, int ws) {
+__global__ void __launch_bounds__(256) k_tadj_ht(const DomDev<T>* __restrict__ dp, int band, int rs, int ws) {
     const DomDev<T>& d = *dp;
     int i, j, k;
-    if (!node_at(d, i, j, k)) return;
+    if (!node_at(d, band, i, j, k)) return;
     const long long wo = (long long)ws * d.as, ro = (long long)rs * d.as, f = fidx(d, i, j, k);
     T et[3];
     const bool clear = i > d.L[0][0] && i < d.n[0] - d.L[0][1] && j > d.L[1][0] && j < d.n[1] - d.L[1][1] && k > d.L[2][0] &&
@@ -170,10 +175,10 @@ __device__ __forceinline__ T back_val(const DomDev<T>& d, const FDTD_GLOBAL T* F
 // 200^3: 375 us so in 64 x 4 tiles, 243 in the numbering of node_at, where the
 // FP64 gradient of 6 entries alone moves 560 MB.)
 template <typename T, bool PER>
-__global__ void __launch_bounds__(256) k_tadj_e(const DomDev<T>* __restrict__ dp, int rs, int ws, int fsr) {
+__global__ void __launch_bounds__(256) k_tadj_e(const DomDev<T>* __restrict__ dp, int band, int rs, int ws, int fsr) {
     const DomDev<T>& d = *dp;
     int i, j, k;
-    if (!node_at(d, i, j, k)) return;
+    if (!node_at(d, band, i, j, k)) return;
     const long long wo = (long long)ws * d.as;
     const FDTD_GLOBAL T* ex = gp(d.Ea[0]) + wo;
     const FDTD_GLOBAL T* ey = gp(d.Ea[1]) + wo;
@@ -296,11 +301,11 @@ __global__ void __launch_bounds__(256) k_tadj_e(const DomDev<T>* __restrict__ dp
 template <typename T>
 void launch_tens_adj(const void* doms, int dom, const int n[3], int rs, int ws, int fsr, bool per, hipStream_t s) {
     const DomDev<T>* dp = (const DomDev<T>*)doms + dom;
-    const unsigned nb = (unsigned)(((long long)n[0] * n[1] + 255) / 256);
-    const dim3 grid(nb * (unsigned)n[2]);
-    hipLaunchKernelGGL(k_tadj_ht<T>, grid, dim3(256), 0, s, dp, rs, ws);
-    if (per) hipLaunchKernelGGL((k_tadj_e<T, true>), grid, dim3(256), 0, s, dp, rs, ws, fsr);
-    else hipLaunchKernelGGL((k_tadj_e<T, false>), grid, dim3(256), 0, s, dp, rs, ws, fsr);
+    const int nb = (int)(((long long)n[0] * n[1] + 255) / 256), bands = (nb + 127) / 128, band = (nb + bands - 1) / bands;
+    const dim3 grid((unsigned)bands * (unsigned)band * (unsigned)n[2]);
+    hipLaunchKernelGGL(k_tadj_ht<T>, grid, dim3(256), 0, s, dp, band, rs, ws);
+    if (per) hipLaunchKernelGGL((k_tadj_e<T, true>), grid, dim3(256), 0, s, dp, band, rs, ws, fsr);
+    else hipLaunchKernelGGL((k_tadj_e<T, false>), grid, dim3(256), 0, s, dp, band, rs, ws, fsr);
 }
 
 template void launch_tens_adj<float>(const void*, int, const int*, int, int, int, bool, hipStream_t);

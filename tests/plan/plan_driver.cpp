@@ -241,7 +241,7 @@ int check_spans(const Case& c) {
     if (!plan(h, c)) return 0;
     Arena ar[4];
     for (int q = 0; q < 4; ++q) {
-        ar[q].base = (char*)0 + ((size_t)(q + 1) << 44);   // never read
+        ar[q].base = (char*)((size_t)(q + 1) << 44);   // never read
         ar[q].assign = true;
     }
     h.layout(ar[0], ar[1], ar[2], ar[3]);
